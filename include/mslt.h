@@ -238,7 +238,7 @@ int mslt_profile_read(mslt_model* m, mslt_profile_entry* out, int cap, int* n);
  * through one chosen kernel, enqueued on hip_stream (hipStream_t as void*, null = default stream).
  * A and B are bf16 (2 bytes per element, round to nearest even); a_kcontig != 0: A(m,k) = A[m*K + k],
  * else A[k*M + m]; the same for B with n and N.  C is row-major [M,N], bf16, or fp32 when out_f32 != 0.
- * kernel 0: guarded SIMT kernel (any shape).  kernel 1: 128-wide MFMA kernel, tile_m 0 (chosen by
+ * kernel 0: guarded kernel (any shape).  kernel 1: 128-wide MFMA kernel, tile_m 0 (chosen by
  * shape), 128 or 256; M % 128 == 0, N % 128 == 0, K % 64 == 0.  kernel 2: large-tile kernel fed by
  * direct global-to-LDS loads, tile_m x tile_n one of 256x256, 256x128, 128x256, 128x128, ring stage
  * tile_k 64 (or 32, not for 128x128); M % tile_m == 0, N % tile_n == 0, K % tile_k == 0.  splitk > 1

@@ -145,8 +145,10 @@ struct GemmDesc {
 };
 
 // dtype: 0 = float operands, 1 = bf16 operands.
-// Guarded SIMT kernel: any shape, any leading dimension.
-hipError_t gemm_simt(int dtype, const GemmDesc& d, hipStream_t s);
+// Guarded kernel: any shape, any leading dimension.  splitk > 1 needs splitk*M*N floats of partials; guarded_splitk
+// gives the factor for a product when that many floats are available.
+int guarded_splitk(int M, int N, int K, int dtype, size_t partial_floats);
+hipError_t gemm_guarded(int dtype, const GemmDesc& d, int splitk, float* partials, hipStream_t s);
 // MFMA kernel (bf16 only): M, N multiples of 128, K multiple of 64 (per split), all loads in
 // bounds by construction (padded buffers).  splitk > 1 writes fp32 partials to `partials`
 // ([splitk][M][N]) and reduces them in fixed order into the epilogue.

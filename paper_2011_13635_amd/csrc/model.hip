@@ -368,7 +368,7 @@ static size_t carve(mslt_model* m, char* base) {
   if (ct > red) red = ct;
   m->red_floats = red;
   m->red_scratch = b.take<float>(red * 4);
-  m->splitk_floats = m->mfma ? (size_t)1024 * 128 * 128 : 0;
+  m->splitk_floats = (size_t)1024 * (m->mfma ? 128 * 128 : 64 * 64);   // as many tiles as split products have at most
   m->splitk = b.take<float>(m->splitk_floats * 4);
   m->splitk2 = b.take<float>(m->splitk_floats * 4);
   m->red2 = b.take<float>(red * 4);
@@ -761,7 +761,8 @@ static int run_gemm(mslt_model* m, const GemmDesc& d, bool allow_splitk = false,
     while (sk > 1 && (size_t)sk * d.M * d.N > m->splitk_floats) --sk;
     HIP_TRY(gemm_mfma(d, sk, partials, st));
   } else {
-    HIP_TRY(gemm_simt(m->dtype, d, st));
+    const int sk = partials ? guarded_splitk(d.M, d.N, d.K, m->dtype, m->splitk_floats) : 1;
+    HIP_TRY(gemm_guarded(m->dtype, d, sk, partials, st));
   }
   return MSLT_OK;
 }
@@ -1475,7 +1476,7 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
   d.lda = d.a_kcontig ? K : M; d.ldb = d.b_kcontig ? K : N;
   d.epi.out = C; d.epi.ldo = N; d.epi.out_f32 = out_f32 != 0;
   if (kernel == 0) {
-    HIP_TRY(gemm_simt(1, d, st));
+    HIP_TRY(gemm_guarded(1, d, 1, nullptr, st));
   } else if (kernel == 1) {
     if (!gemm_mfma_supported(d) || (tile_m != 0 && tile_m != 128 && tile_m != 256) || (tile_m && M % tile_m) || splitk > K / 64)
       return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d (tile_m %d, splitk %d) not taken by the 128-wide kernel", M, N, K,

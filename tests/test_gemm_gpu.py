@@ -61,6 +61,18 @@ def test_guarded_kernel_takes_ragged_shapes_and_agrees():
         assert np.abs(c.cpu().numpy() - ref).max() <= 1e-6 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (2, 64, 63), (63, 65, 64), (64, 64, 128), (65, 2, 129), (200, 130, 9)])
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
+def test_guarded_kernel_at_tile_edges(M, N, K, akc, bkc):
+    # products and partial sums of these operands are exact in fp32 (multiples of 2^-8, sums below 2^16)
+    import torch
+    ta, tb, ref = _operands(torch, M, N, K, akc, bkc, seed=20 + M)
+    c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda:0")
+    binding.mslt_debug_gemm(ta, tb, c, M, N, K, akc, bkc, 0)
+    torch.cuda.synchronize()
+    assert np.array_equal(c.cpu().numpy().astype(np.float64), ref)
+
+
 def test_unsupported_choices_are_refused_without_work():
     import torch
     ta, tb, _ = _operands(torch, 256, 256, 128, 1, 1, seed=3)
