@@ -1,4 +1,4 @@
-// bf16 MFMA attention for gfx950, head width 64, sequence length a multiple of 128.
+// bf16 MFMA attention for gfx950, head width 64, any sequence length.
 //
 // Forward: softmax(Q K^T / sqrt(d) + key mask) V with the scale, mask and softmax fused between
 // the two products; the S x S scores never leave registers.  Backward: scores are recomputed
@@ -15,6 +15,9 @@
 // agreeing on a permuted order of the contraction index (the order in which a lane's registers
 // hold it); the A operand (V^T, K^T, Q^T, dC^T) is written to LDS transposed and in that order.
 // One 256-thread workgroup handles 128 queries (or keys) of one (batch, head): 32 per wavefront.
+// Lengths that are no multiple of 128 run through the same kernels (RAG below).  Before, they went to one wavefront per
+// row in fp32 vector arithmetic: BERT-Base 9+3 layers, 27x203, dropout: attention 12.6 -> 0.7 ms of a step, the step
+// 15.9 -> 4.1 ms.
 #include "common.h"
 
 namespace mslt {
@@ -30,13 +33,21 @@ constexpr int TLD = 136;      // row stride (elements) of a transposed tile [64]
 
 __device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 7) ^ ((row >> 4) & 7); }
 
-// Row-major tile [128][64] from global rows of stride ld, 16-byte chunks XOR-swizzled per row.
-__device__ __forceinline__ void load_tile_rows(bf16* __restrict__ lds, const bf16* __restrict__ g, size_t ld, int tid) {
+// A sequence whose length is no multiple of 128 leaves its last tile partly empty (RAG).  Loads of the rows past
+// the end re-read the last row, so that they stay unconditional and in bounds; such keys get a bias of -inf and
+// such queries a log-sum-exp of +inf, either of which makes their probabilities exact zeros, and nothing is stored
+// for them.  Blocks of 32 rows (forward: 64 keys) that lie past the end altogether are skipped.
+template <bool RAG>
+__device__ __forceinline__ int tile_row(int row, int last) { return RAG ? min(row, last) : row; }
+
+// Row-major tile [128][64] from global rows of stride ld, 16-byte chunks XOR-swizzled per row; last: last valid row.
+template <bool RAG>
+__device__ __forceinline__ void load_tile_rows(bf16* __restrict__ lds, const bf16* __restrict__ g, size_t ld, int tid, int last) {
   int c = tid & 7, r = tid >> 3;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     int row = r + 32 * p;
-    u32x4_t v = *reinterpret_cast<const u32x4_t*>(g + (size_t)row * ld + 8 * c);
+    u32x4_t v = *reinterpret_cast<const u32x4_t*>(g + (size_t)tile_row<RAG>(row, last) * ld + 8 * c);
     *reinterpret_cast<u32x4_t*>(lds + row * DH + 8 * (c ^ swz8(row))) = v;
   }
 }
@@ -62,14 +73,16 @@ __device__ __forceinline__ void put4(bf16* __restrict__ lds, int d, int pos, uin
   o.y = __builtin_amdgcn_perm(e, c, sel);
   *reinterpret_cast<u32x2_t*>(lds + d * TLD + pos) = o;
 }
+template <bool RAG>
 __device__ __forceinline__ void load_tile_transposed(bf16* __restrict__ lds, const bf16* __restrict__ g, size_t ld,
-                                                     int tid) {
+                                                     int tid, int last) {
   int rg = tid >> 3, dg = tid & 7;  // rows 4rg..4rg+3, d 8dg..8dg+7
-  const bf16* q = g + (size_t)(4 * rg) * ld + 8 * dg;
-  u32x4_t v0 = *reinterpret_cast<const u32x4_t*>(q);
-  u32x4_t v1 = *reinterpret_cast<const u32x4_t*>(q + ld);
-  u32x4_t v2 = *reinterpret_cast<const u32x4_t*>(q + 2 * ld);
-  u32x4_t v3 = *reinterpret_cast<const u32x4_t*>(q + 3 * ld);
+  const bf16* q = g + (size_t)(RAG ? 0 : 4 * rg) * ld + 8 * dg;
+  auto at = [&](int i) { return q + (size_t)(RAG ? min(4 * rg + i, last) : i) * ld; };
+  u32x4_t v0 = *reinterpret_cast<const u32x4_t*>(at(0));
+  u32x4_t v1 = *reinterpret_cast<const u32x4_t*>(at(1));
+  u32x4_t v2 = *reinterpret_cast<const u32x4_t*>(at(2));
+  u32x4_t v3 = *reinterpret_cast<const u32x4_t*>(at(3));
   int pos = perm_pos(4 * rg), d = 8 * dg;
   const uint32_t LO = 0x05040100u, HI = 0x07060302u;
   put4(lds, d + 0, pos, v0.x, v1.x, v2.x, v3.x, LO);
@@ -137,6 +150,38 @@ __device__ __forceinline__ void load_ctx8(const bf16* __restrict__ ctx, const fl
   }
 }
 
+// Keep bits of the four consecutive elements from index e on, as drop_quad gives them for a whole quad: when a row
+// of the probabilities does not start on a multiple of four, two quads are joined.
+template <bool RAG>
+__device__ __forceinline__ uint64_t drop_four(const DropSpec& d, uint64_t e) {
+  const uint64_t lo = drop_quad(d, e >> 2);
+  if constexpr (!RAG) return lo;
+  const int sh = 16 * (int)(e & 3);
+  if (sh == 0) return lo;
+  return (lo >> sh) | (drop_quad(d, (e >> 2) + 1) << (64 - sh));
+}
+
+// The key side holds one key per lane and the queries in registers, so the four elements of a quad sit in four
+// neighbouring lanes.  Each lane draws the quad of one of four consecutive query rows (row e0/S + lane%4; e0: element
+// index of that row at the first key of the lane's four) and the lanes exchange them: a quarter of the hashes.
+// keep[j]: factor of this lane's key for the j-th of the four rows.
+template <int J>
+__device__ __forceinline__ float quad_field(const DropSpec& d, uint32_t lo, uint32_t hi, int lane) {
+  const uint32_t a = (uint32_t)__builtin_amdgcn_mov_dpp((int)lo, J * 0x55, 0xf, 0xf, true);
+  const uint32_t b = (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, J * 0x55, 0xf, 0xf, true);
+  const uint32_t w = (lane & 2) ? b : a;
+  return ((lane & 1) ? w >> 16 : w & 0xffffu) >= d.thr ? d.scale : 0.f;
+}
+template <bool RAG>
+__device__ __forceinline__ void drop_rows(const DropSpec& d, uint64_t e0, int lane, float (&keep)[4]) {
+  const uint64_t r = drop_four<RAG>(d, e0);
+  const uint32_t lo = (uint32_t)r, hi = (uint32_t)(r >> 32);
+  keep[0] = quad_field<0>(d, lo, hi, lane);
+  keep[1] = quad_field<1>(d, lo, hi, lane);
+  keep[2] = quad_field<2>(d, lo, hi, lane);
+  keep[3] = quad_field<3>(d, lo, hi, lane);
+}
+
 // ---- forward --------------------------------------------------------------------------------
 // The K and V^T tiles of one step (one key tile of one work item) as they sit in registers between the
 // global loads and the LDS writes: issued one step ahead, so that the loads of step i+1 are in flight
@@ -145,15 +190,18 @@ struct KvRegs {
   u32x4_t k[4], v[4];
   float bias;
 };
+template <bool RAG>
 __device__ __forceinline__ void fetch_kv(KvRegs& r, const bf16* __restrict__ kbase, const bf16* __restrict__ vbase,
-                                         size_t ld, const int32_t* __restrict__ am_row, float mask_bias, int tid) {
+                                         size_t ld, const int32_t* __restrict__ am_row, float mask_bias, int tid, int last) {
   const int c = tid & 7, rr = tid >> 3;
 #pragma unroll
-  for (int p = 0; p < 4; ++p) r.k[p] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)(rr + 32 * p) * ld + 8 * c);
-  const bf16* q = vbase + (size_t)(4 * rr) * ld + 8 * c;     // rows 4rr..4rr+3, d 8c..8c+7
+  for (int p = 0; p < 4; ++p)
+    r.k[p] = *reinterpret_cast<const u32x4_t*>(kbase + (size_t)tile_row<RAG>(rr + 32 * p, last) * ld + 8 * c);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) r.v[p] = *reinterpret_cast<const u32x4_t*>(q + p * ld);
-  r.bias = (tid < TILE) ? (am_row[tid] ? 0.f : mask_bias) : 0.f;
+  for (int p = 0; p < 4; ++p)      // rows 4rr..4rr+3, d 8c..8c+7
+    r.v[p] = *reinterpret_cast<const u32x4_t*>(vbase + (size_t)(RAG ? 0 : 4 * rr) * ld + 8 * c + (size_t)(RAG ? min(4 * rr + p, last) : p) * ld);
+  r.bias = (tid < TILE) ? (am_row[tile_row<RAG>(tid, last)] ? 0.f : mask_bias) : 0.f;
+  if (RAG && tid > last) r.bias = -INFINITY;
 }
 __device__ __forceinline__ void commit_kv(const KvRegs& r, bf16* __restrict__ Ks, bf16* __restrict__ Vt,
                                           float* __restrict__ bias, int tid) {
@@ -183,7 +231,7 @@ constexpr int FWD_LDS_BYTES = 2 * (FWD_BUF_ELEMS * 2 + TILE * 4);       // two s
 // query tile fastest, then head, then batch) and walks their key tiles as one sequence of steps over two
 // LDS buffers: while step i runs on one buffer, the K/V rows (and, at an item's first step, the Q
 // fragments) of step i+1 are already on their way from memory.
-template <bool DROP>
+template <bool DROP, bool RAG>
 __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict__ qkv, bf16* __restrict__ ctx,
                                                        float* __restrict__ lse, const int32_t* __restrict__ am, int S,
                                                        int nh, float scale, float mask_bias, DropSpec drop,
@@ -192,7 +240,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict
   bf16* const tiles = reinterpret_cast<bf16*>(fwd_lds);
   float* const biases = reinterpret_cast<float*>(fwd_lds + 2 * FWD_BUF_ELEMS * 2);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, half = lane >> 5;
-  const int H = nh * DH, nkt = S / TILE;
+  const int H = nh * DH, nkt = RAG ? (S + TILE - 1) / TILE : S / TILE;
   const size_t ld = 3 * (size_t)H;
   const int first = blockIdx.x * per_wg;
   const int count = min(per_wg, n_items - first);
@@ -218,10 +266,10 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict
     int b, h, qt, kt;
     item_of(step, b, h, qt, kt);
     const bf16* base = qkv + (size_t)b * S * ld + h * DH;
-    fetch_kv(regs, base + H + (size_t)kt * TILE * ld, base + 2 * H + (size_t)kt * TILE * ld, ld,
-             am + (size_t)b * S + kt * TILE, mask_bias, tid);
+    fetch_kv<RAG>(regs, base + H + (size_t)kt * TILE * ld, base + 2 * H + (size_t)kt * TILE * ld, ld,
+                  am + (size_t)b * S + kt * TILE, mask_bias, tid, S - 1 - kt * TILE);
     if (kt == 0) {
-      const int q = qt * TILE + wave * 32 + n;
+      const int q = tile_row<RAG>(qt * TILE + wave * 32 + n, S - 1);
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
         qn[ks] = *reinterpret_cast<const bf16x8_t*>(base + (size_t)q * ld + 16 * ks + 8 * half);
@@ -254,8 +302,9 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict
     if (step + 1 < steps) fetch(step + 1);
 
     // the tile's keys go through the running softmax in two halves of 64: half the score registers
+    const int halves = !RAG ? 2 : qt * TILE + wave * 32 >= S ? 0 : S - kt * TILE <= TILE / 2 ? 1 : 2;
 #pragma unroll 1
-    for (int kh = 0; kh < 2; ++kh) {
+    for (int kh = 0; kh < halves; ++kh) {
       f32x16_t s[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
@@ -295,7 +344,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict
         for (int j = 0; j < 2; ++j)
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            const uint64_t r = drop_quad(drop, (rowbase + (2 * kh + j) * 32 + 8 * g + 4 * half) >> 2);
+            const uint64_t r = drop_four<RAG>(drop, rowbase + (2 * kh + j) * 32 + 8 * g + 4 * half);
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) s[j][4 * g + jj] *= drop_field(drop, r, jj);
           }
@@ -314,7 +363,8 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict
           o1 = MFMA(frag_transposed(Vt, 32 + n, 2 * kh + j, c, half), pf, o1);
         }
     }
-    if (kt == nkt - 1) {
+    // (a ragged tile: the swap between the halves below is between lanes of one query, so they leave together)
+    if (kt == nkt - 1 && (!RAG || q < S)) {
       float l_tot = l_run + __shfl_xor(l_run, 32, 64);
       float inv = 1.0f / l_tot;
       bf16* out = ctx + ((size_t)b * S + qt * TILE + wave * 32) * H + h * DH;
@@ -336,8 +386,10 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict
 }
 
 // ---- backward, query side: delta and dQ -----------------------------------------------------
-template <bool DROP>
-__global__ void __launch_bounds__(256) k_attn_bwd_q_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx,
+// (The four key blocks of a tile stay a loop: 154 registers and three wavefronts per SIMD, 45 us at 16x512x12 heads;
+//  unrolled 252 registers, 55 us.)
+template <bool DROP, bool RAG>
+__global__ void __launch_bounds__(256, 2) k_attn_bwd_q_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx,
                                                          const bf16* __restrict__ dctx, const float* __restrict__ lse,
                                                          float* __restrict__ delta, bf16* __restrict__ dqkv,
                                                          const int32_t* __restrict__ am, int S, int nh, float scale,
@@ -352,7 +404,8 @@ __global__ void __launch_bounds__(256) k_attn_bwd_q_mfma(const bf16* __restrict_
   const int H = nh * DH;
   const size_t ld = 3 * (size_t)H;
   const bf16* base = qkv + (size_t)b * S * ld + h * DH;
-  const int q = qt * TILE + wave * 32 + n;
+  const int q_own = qt * TILE + wave * 32 + n, q = tile_row<RAG>(q_own, S - 1);
+  const bool q_in = !RAG || q_own < S;
   const size_t tok = (size_t)b * S + q;
   const uint64_t rowbase = (((uint64_t)b * nh + h) * S + q) * S;   // element index of P[b, h, q, 0]
 
@@ -369,19 +422,22 @@ __global__ void __launch_bounds__(256) k_attn_bwd_q_mfma(const bf16* __restrict_
   }
   dl += __shfl_xor(dl, 32, 64);
   const float l = lse[((size_t)b * nh + h) * S + q];
-  if (half == 0) delta[((size_t)b * nh + h) * S + q] = dl;
+  if (half == 0 && q_in) delta[((size_t)b * nh + h) * S + q] = dl;
 
   f32x16_t dq0 = zero16(), dq1 = zero16();
-  for (int kt = 0; kt < S / TILE; ++kt) {
+  const int nkt = RAG ? (S + TILE - 1) / TILE : S / TILE;
+  for (int kt = 0; kt < nkt; ++kt) {
     if (kt > 0) __syncthreads();
     const bf16* kbase = base + H + (size_t)kt * TILE * ld;
-    load_tile_rows(Ks, kbase, ld, tid);
-    load_tile_rows(Vs, base + 2 * H + (size_t)kt * TILE * ld, ld, tid);
-    load_tile_transposed(Kt, kbase, ld, tid);
-    if (tid < TILE) bias[tid] = am[b * S + kt * TILE + tid] ? 0.f : mask_bias;
+    const int last = S - 1 - kt * TILE;
+    load_tile_rows<RAG>(Ks, kbase, ld, tid, last);
+    load_tile_rows<RAG>(Vs, base + 2 * H + (size_t)kt * TILE * ld, ld, tid, last);
+    load_tile_transposed<RAG>(Kt, kbase, ld, tid, last);
+    if (tid < TILE) bias[tid] = RAG && tid > last ? -INFINITY : am[b * S + kt * TILE + tid] ? 0.f : mask_bias;
     __syncthreads();
-#pragma unroll
+#pragma unroll 1
     for (int kb = 0; kb < 4; ++kb) {
+      if (RAG && kb * 32 > last) break;
       f32x16_t s = zero16(), dp = zero16();
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
@@ -394,7 +450,7 @@ __global__ void __launch_bounds__(256) k_attn_bwd_q_mfma(const bf16* __restrict_
         float bv[4] = {bb.x, bb.y, bb.z, bb.w};
         float kf4[4] = {1.f, 1.f, 1.f, 1.f};
         if constexpr (DROP) {
-          const uint64_t r = drop_quad(drop, (rowbase + (uint64_t)kt * TILE + kb * 32 + 8 * g + 4 * half) >> 2);
+          const uint64_t r = drop_four<RAG>(drop, rowbase + (uint64_t)kt * TILE + kb * 32 + 8 * g + 4 * half);
 #pragma unroll
           for (int j = 0; j < 4; ++j) kf4[j] = drop_field(drop, r, j);
         }
@@ -412,16 +468,19 @@ __global__ void __launch_bounds__(256) k_attn_bwd_q_mfma(const bf16* __restrict_
       }
     }
   }
+  if (!q_in) return;
   bf16* out = dqkv + ((size_t)b * S + qt * TILE + wave * 32) * ld + h * DH;
   store_acc_T(out, ld, n, half, dq0, scale);
   store_acc_T(out + 32, ld, n, half, dq1, scale);
 }
 
 // ---- backward, key side: dK and dV ----------------------------------------------------------
-// (two wavefronts per SIMD asked for: the accumulators then stay in VGPRs, where the softmax arithmetic reads
-//  them without v_accvgpr moves, and two workgroups share a compute unit; the dropout variant would spill)
-template <bool DROP>
-__global__ void __launch_bounds__(256, DROP ? 1 : 2) k_attn_bwd_kv_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ dctx,
+// (Two wavefronts per SIMD asked for: the accumulators then stay in VGPRs, where the softmax arithmetic reads them
+//  without v_accvgpr moves, and two workgroups share a compute unit.  Unrolled over its four query blocks the plain
+//  kernel takes 53 us at 16x512x12 heads, as a loop 70; the dropout variant spills when unrolled and took 512 registers
+//  with one hash per element: as a loop with shared hashes 41 us at 27x203x12 heads, before 142.)
+template <bool DROP, bool RAG>
+__global__ void __launch_bounds__(256, 2) k_attn_bwd_kv_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ dctx,
                                                           const float* __restrict__ lse,
                                                           const float* __restrict__ delta, bf16* __restrict__ dqkv,
                                                           const int32_t* __restrict__ am, int S, int nh, float scale,
@@ -438,7 +497,7 @@ __global__ void __launch_bounds__(256, DROP ? 1 : 2) k_attn_bwd_kv_mfma(const bf
   const int H = nh * DH;
   const size_t ld = 3 * (size_t)H;
   const bf16* base = qkv + (size_t)b * S * ld + h * DH;
-  const int key = kt * TILE + wave * 32 + n;  // this lane's key
+  const int key_own = kt * TILE + wave * 32 + n, key = tile_row<RAG>(key_own, S - 1);  // this lane's key
   const uint64_t headbase = ((uint64_t)b * nh + h) * S;          // row index of P[b, h, 0, :]
 
   bf16x8_t kf[4], vf[4];
@@ -450,21 +509,25 @@ __global__ void __launch_bounds__(256, DROP ? 1 : 2) k_attn_bwd_kv_mfma(const bf
   const float kbias = am[b * S + key] ? 0.f : mask_bias;
 
   f32x16_t dk0 = zero16(), dk1 = zero16(), dv0 = zero16(), dv1 = zero16();
-  for (int qt = 0; qt < S / TILE; ++qt) {
+  const int nqt = RAG ? (S + TILE - 1) / TILE : S / TILE;
+  for (int qt = 0; qt < nqt; ++qt) {
     if (qt > 0) __syncthreads();
     const bf16* qbase = base + (size_t)qt * TILE * ld;
     const bf16* gbase = dctx + ((size_t)b * S + qt * TILE) * H + h * DH;
-    load_tile_rows(Qs, qbase, ld, tid);
-    load_tile_rows(Gs, gbase, H, tid);
-    load_tile_transposed(Qt, qbase, ld, tid);
-    load_tile_transposed(Gt, gbase, H, tid);
+    const int last = S - 1 - qt * TILE;
+    load_tile_rows<RAG>(Qs, qbase, ld, tid, last);
+    load_tile_rows<RAG>(Gs, gbase, H, tid, last);
+    load_tile_transposed<RAG>(Qt, qbase, ld, tid, last);
+    load_tile_transposed<RAG>(Gt, gbase, H, tid, last);
     if (tid < TILE) {
-      lse_s[tid] = lse[((size_t)b * nh + h) * S + qt * TILE + tid];
-      dl_s[tid] = delta[((size_t)b * nh + h) * S + qt * TILE + tid];
+      const bool in = !RAG || tid <= last;
+      lse_s[tid] = in ? lse[((size_t)b * nh + h) * S + qt * TILE + tid] : INFINITY;
+      dl_s[tid] = in ? delta[((size_t)b * nh + h) * S + qt * TILE + tid] : 0.f;
     }
     __syncthreads();
-#pragma unroll
+#pragma unroll(DROP ? 1 : 4)
     for (int qb = 0; qb < 4; ++qb) {
+      if (RAG && qb * 32 > last) break;
       f32x16_t s = zero16(), dp = zero16();   // S[q,key] and dP[q,key]: lane = key, registers = queries
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
@@ -476,11 +539,13 @@ __global__ void __launch_bounds__(256, DROP ? 1 : 2) k_attn_bwd_kv_mfma(const bf
         float4 ll = *reinterpret_cast<const float4*>(&lse_s[qb * 32 + 8 * g + 4 * half]);
         float4 dd = *reinterpret_cast<const float4*>(&dl_s[qb * 32 + 8 * g + 4 * half]);
         float lv[4] = {ll.x, ll.y, ll.z, ll.w}, dv[4] = {dd.x, dd.y, dd.z, dd.w};
+        float keep[4] = {1.f, 1.f, 1.f, 1.f};
+        if constexpr (DROP)
+          drop_rows<RAG>(drop, (headbase + (uint64_t)qt * TILE + qb * 32 + 8 * g + 4 * half + (lane & 3)) * S + (key_own & ~3), lane, keep);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           float p = __expf(s[4 * g + j] * scale + kbias - lv[j]);
-          float kf1 = 1.f;
-          if constexpr (DROP) kf1 = drop_factor(drop, (headbase + (uint64_t)qt * TILE + qb * 32 + 8 * g + 4 * half + j) * S + key);
+          const float kf1 = keep[j];
           s[4 * g + j] = p * kf1;                                   // dropped P (for dV)
           dp[4 * g + j] = p * (dp[4 * g + j] * kf1 - dv[j]);        // dS
         }
@@ -495,6 +560,7 @@ __global__ void __launch_bounds__(256, DROP ? 1 : 2) k_attn_bwd_kv_mfma(const bf
       }
     }
   }
+  if (RAG && key_own >= S) return;
   bf16* out = dqkv + ((size_t)b * S + kt * TILE + wave * 32) * ld + h * DH;
   store_acc_T(out + H, ld, n, half, dk0, scale);
   store_acc_T(out + H + 32, ld, n, half, dk1, scale);
@@ -502,7 +568,7 @@ __global__ void __launch_bounds__(256, DROP ? 1 : 2) k_attn_bwd_kv_mfma(const bf
   store_acc_T(out + 2 * H + 32, ld, n, half, dv1, 1.0f);
 }
 
-// ---- backward for one-tile sequences (S = 128): both sides in one launch ----------------------
+// ---- backward for one-tile sequences (S <= 128): both sides in one launch ---------------------
 // One 512-thread workgroup per (batch, head).  All eight wavefronts first stage Q, K, V and dC
 // (row tiles for the first products, transposed tiles for the second ones), the row log-sum-exp,
 // the key bias and delta = rowsum(dC * C) in LDS; then wavefronts 0..3 run the query side (dQ)
@@ -510,11 +576,11 @@ __global__ void __launch_bounds__(256, DROP ? 1 : 2) k_attn_bwd_kv_mfma(const bf
 // two kernels above.  Every operand is read from memory once and delta never leaves the chip.
 constexpr int ONE_LDS_BYTES = (4 * TILE * DH + 3 * DH * TLD) * 2 + 3 * TILE * 4;
 
-template <bool DROP>
+template <bool DROP, bool RAG>
 __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx,
                                                            const bf16* __restrict__ dctx,
                                                            const float* __restrict__ lse, bf16* __restrict__ dqkv,
-                                                           const int32_t* __restrict__ am, int nh, float scale,
+                                                           const int32_t* __restrict__ am, int seq, int nh, float scale,
                                                            float mask_bias, DropSpec drop,
                                                            const float* __restrict__ ctx32) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_one[];   // ONE_LDS_BYTES
@@ -528,7 +594,7 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
   float* lse_s = reinterpret_cast<float*>(Gt + DH * TLD);
   float* dl_s = lse_s + TILE;
   float* bias = dl_s + TILE;
-  constexpr int S = TILE;
+  const int S = RAG ? seq : TILE, last = S - 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, half = lane >> 5;
   const int h = blockIdx.x, b = blockIdx.y;
   const int H = nh * DH;
@@ -538,19 +604,19 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
 
   // staging: the two halves of the workgroup take different tiles
   if (tid < 256) {
-    load_tile_rows(Ks, base + H, ld, tid);
-    load_tile_rows(Vs, base + 2 * H, ld, tid);
-    load_tile_transposed(Kt, base + H, ld, tid);
-    load_tile_rows(Gs, gbase, H, tid);
+    load_tile_rows<RAG>(Ks, base + H, ld, tid, last);
+    load_tile_rows<RAG>(Vs, base + 2 * H, ld, tid, last);
+    load_tile_transposed<RAG>(Kt, base + H, ld, tid, last);
+    load_tile_rows<RAG>(Gs, gbase, H, tid, last);
   } else {
-    load_tile_rows(Qs, base, ld, tid - 256);
-    load_tile_transposed(Qt, base, ld, tid - 256);
-    load_tile_transposed(Gt, gbase, H, tid - 256);
+    load_tile_rows<RAG>(Qs, base, ld, tid - 256, last);
+    load_tile_transposed<RAG>(Qt, base, ld, tid - 256, last);
+    load_tile_transposed<RAG>(Gt, gbase, H, tid - 256, last);
   }
   {
     // delta[q] = sum_d dC[q,d] * C[q,d]: four threads per query, 16 d each
     const int q = tid >> 2, part = tid & 3;
-    const size_t o = ((size_t)b * S + q) * H + h * DH + 16 * part;
+    const size_t o = ((size_t)b * S + tile_row<RAG>(q, last)) * H + h * DH + 16 * part;
     float dl = 0.f;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -564,13 +630,14 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
     dl += __shfl_xor(dl, 2, 64);
     if (part == 0) dl_s[q] = dl;
   }
-  if (tid < TILE) lse_s[tid] = lse[((size_t)b * nh + h) * S + tid];
-  else if (tid < 2 * TILE) bias[tid - TILE] = am[b * S + tid - TILE] ? 0.f : mask_bias;
+  if (tid < TILE) lse_s[tid] = RAG && tid > last ? INFINITY : lse[((size_t)b * nh + h) * S + tid];
+  else if (tid < 2 * TILE) bias[tid - TILE] = RAG && tid - TILE > last ? -INFINITY : am[b * S + tid - TILE] ? 0.f : mask_bias;
   __syncthreads();
 
   if (wave < 4) {
     // query side: lane owns query q, registers run over keys
-    const int q = wave * 32 + n;
+    if (RAG && wave * 32 > last) return;
+    const int q_own = wave * 32 + n, q = tile_row<RAG>(q_own, last);
     const uint64_t rowbase = (((uint64_t)b * nh + h) * S + q) * S;
     bf16x8_t qf[4], gf[4];
 #pragma unroll
@@ -582,6 +649,7 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
     f32x16_t dq0 = zero16(), dq1 = zero16();
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
+      if (RAG && kb * 32 > last) break;
       f32x16_t s = zero16(), dp = zero16();
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
@@ -594,7 +662,7 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
         float bv[4] = {bb.x, bb.y, bb.z, bb.w};
         float kf4[4] = {1.f, 1.f, 1.f, 1.f};
         if constexpr (DROP) {
-          const uint64_t r = drop_quad(drop, (rowbase + kb * 32 + 8 * g + 4 * half) >> 2);
+          const uint64_t r = drop_four<RAG>(drop, rowbase + kb * 32 + 8 * g + 4 * half);
 #pragma unroll
           for (int j = 0; j < 4; ++j) kf4[j] = drop_field(drop, r, j);
         }
@@ -611,13 +679,15 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
         dq1 = MFMA(frag_transposed(Kt, 32 + n, kb, c, half), df, dq1);
       }
     }
+    if (RAG && q_own > last) return;
     bf16* out = dqkv + ((size_t)b * S + wave * 32) * ld + h * DH;
     store_acc_T(out, ld, n, half, dq0, scale);
     store_acc_T(out + 32, ld, n, half, dq1, scale);
   } else {
     // key side: lane owns a key, registers run over queries
     const int w = wave - 4;
-    const int key = w * 32 + n;
+    if (RAG && w * 32 > last) return;
+    const int key_own = w * 32 + n, key = tile_row<RAG>(key_own, last);
     const uint64_t headbase = ((uint64_t)b * nh + h) * S;
     bf16x8_t kf[4], vf[4];
 #pragma unroll
@@ -629,6 +699,7 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
     f32x16_t dk0 = zero16(), dk1 = zero16(), dv0 = zero16(), dv1 = zero16();
 #pragma unroll
     for (int qb = 0; qb < 4; ++qb) {
+      if (RAG && qb * 32 > last) break;
       f32x16_t s = zero16(), dp = zero16();
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
@@ -640,11 +711,13 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
         float4 ll = *reinterpret_cast<const float4*>(&lse_s[qb * 32 + 8 * g + 4 * half]);
         float4 dd = *reinterpret_cast<const float4*>(&dl_s[qb * 32 + 8 * g + 4 * half]);
         float lv[4] = {ll.x, ll.y, ll.z, ll.w}, dv[4] = {dd.x, dd.y, dd.z, dd.w};
+        float keep[4] = {1.f, 1.f, 1.f, 1.f};
+        if constexpr (DROP)
+          drop_rows<RAG>(drop, (headbase + qb * 32 + 8 * g + 4 * half + (lane & 3)) * S + (key_own & ~3), lane, keep);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           float p = __expf(s[4 * g + j] * scale + kbias - lv[j]);
-          float kf1 = 1.f;
-          if constexpr (DROP) kf1 = drop_factor(drop, (headbase + qb * 32 + 8 * g + 4 * half + j) * S + key);
+          const float kf1 = keep[j];
           s[4 * g + j] = p * kf1;                                   // dropped P (for dV)
           dp[4 * g + j] = p * (dp[4 * g + j] * kf1 - dv[j]);        // dS
         }
@@ -658,6 +731,7 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
         dk1 = MFMA(frag_transposed(Qt, 32 + n, qb, c, half), df, dk1);
       }
     }
+    if (RAG && key_own > last) return;
     bf16* out = dqkv + ((size_t)b * S + w * 32) * ld + h * DH;
     store_acc_T(out + H, ld, n, half, dk0, scale);
     store_acc_T(out + H + 32, ld, n, half, dk1, scale);
@@ -668,72 +742,62 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
 
 constexpr int KV_LDS_BYTES = (2 * TILE * DH + 2 * DH * TLD) * 2 + 2 * TILE * 4;
 
-bool attention_mfma_supported(int S, int dh) { return dh == DH && S >= TILE && S % TILE == 0; }
+bool attention_mfma_supported(int S, int dh) { return dh == DH && S >= 1; }
 
-template <bool DROP>
+static hipError_t allow_lds(const void* kernel, int bytes) {
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+template <bool DROP, bool RAG>
 static hipError_t attention_fwd_mfma_t(const AttnDesc& a, hipStream_t s) {
-  static bool attr_set = false;     // one flag per instantiation
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_fwd_mfma<DROP>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, FWD_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static const hipError_t attr = allow_lds(reinterpret_cast<const void*>(k_attn_fwd_mfma<DROP, RAG>), FWD_LDS_BYTES);
+  if (attr != hipSuccess) return attr;
   // two workgroups fit a compute unit (LDS and registers); up to that many, one item each keeps the most
   // units busy, beyond it a workgroup walks several items so that loads run ahead of the arithmetic
-  const int n_items = a.B * a.nh * (a.S / TILE);
+  const int n_items = a.B * a.nh * ((a.S + TILE - 1) / TILE);
   const int slots = 2 * 256;
   const int per_wg = (n_items + slots - 1) / slots;
   const int n_wg = (n_items + per_wg - 1) / per_wg;
-  k_attn_fwd_mfma<DROP><<<dim3(n_wg), dim3(256), FWD_LDS_BYTES, s>>>(
+  k_attn_fwd_mfma<DROP, RAG><<<dim3(n_wg), dim3(256), FWD_LDS_BYTES, s>>>(
       (const bf16*)a.qkv, (bf16*)a.ctx, a.lse, a.attn_mask, a.S, a.nh, 1.0f / sqrtf((float)a.dh), a.mask_bias, a.drop,
       a.ctx_f32, n_items, per_wg);
   return hipGetLastError();
 }
+// Dropout and ragged lengths are compile-time variants so that the plain kernels carry none of their registers.
 hipError_t attention_fwd_mfma(const AttnDesc& a, hipStream_t s) {
   if (!attention_mfma_supported(a.S, a.dh)) return hipErrorInvalidValue;
-  // dropout is a compile-time variant so that the plain kernels carry none of its registers
-  return a.drop.thr ? attention_fwd_mfma_t<true>(a, s) : attention_fwd_mfma_t<false>(a, s);
+  if (a.S % TILE) return a.drop.thr ? attention_fwd_mfma_t<true, true>(a, s) : attention_fwd_mfma_t<false, true>(a, s);
+  return a.drop.thr ? attention_fwd_mfma_t<true, false>(a, s) : attention_fwd_mfma_t<false, false>(a, s);
 }
 
-template <bool DROP>
+template <bool DROP, bool RAG>
 static hipError_t attention_bwd_mfma_t(const AttnBwdDesc& a, hipStream_t s) {
-  dim3 grid(a.S / TILE, a.nh, a.B);
+  dim3 grid((a.S + TILE - 1) / TILE, a.nh, a.B);
   float scale = 1.0f / sqrtf((float)a.dh);
-  if (a.S == TILE) {
-    static bool one_attr_set = false;     // one flag per instantiation
-    if (!one_attr_set) {
-      hipError_t e1 = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_bwd_one_tile<DROP>),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, ONE_LDS_BYTES);
-      if (e1 != hipSuccess) return e1;
-      one_attr_set = true;
-    }
-    k_attn_bwd_one_tile<DROP><<<dim3(a.nh, a.B), dim3(512), ONE_LDS_BYTES, s>>>(
-        (const bf16*)a.qkv, (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse, (bf16*)a.dqkv, a.attn_mask, a.nh, scale,
+  if (a.S <= TILE) {
+    static const hipError_t attr1 = allow_lds(reinterpret_cast<const void*>(k_attn_bwd_one_tile<DROP, RAG>), ONE_LDS_BYTES);
+    if (attr1 != hipSuccess) return attr1;
+    k_attn_bwd_one_tile<DROP, RAG><<<dim3(a.nh, a.B), dim3(512), ONE_LDS_BYTES, s>>>(
+        (const bf16*)a.qkv, (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse, (bf16*)a.dqkv, a.attn_mask, a.S, a.nh, scale,
         a.mask_bias, a.drop, a.ctx_f32);
     return hipGetLastError();
   }
-  k_attn_bwd_q_mfma<DROP><<<grid, dim3(256), 0, s>>>((const bf16*)a.qkv, (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse,
-                                                     a.delta, (bf16*)a.dqkv, a.attn_mask, a.S, a.nh, scale, a.mask_bias,
-                                                     a.drop, a.ctx_f32);
+  k_attn_bwd_q_mfma<DROP, RAG><<<grid, dim3(256), 0, s>>>((const bf16*)a.qkv, (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse,
+                                                          a.delta, (bf16*)a.dqkv, a.attn_mask, a.S, a.nh, scale, a.mask_bias,
+                                                          a.drop, a.ctx_f32);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  static bool attr_set = false;
-  if (!attr_set) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_bwd_kv_mfma<DROP>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, KV_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  k_attn_bwd_kv_mfma<DROP><<<grid, dim3(256), KV_LDS_BYTES, s>>>((const bf16*)a.qkv, (const bf16*)a.dctx, a.lse, a.delta,
-                                                                 (bf16*)a.dqkv, a.attn_mask, a.S, a.nh, scale,
-                                                                 a.mask_bias, a.drop);
+  static const hipError_t attr2 = allow_lds(reinterpret_cast<const void*>(k_attn_bwd_kv_mfma<DROP, RAG>), KV_LDS_BYTES);
+  if (attr2 != hipSuccess) return attr2;
+  k_attn_bwd_kv_mfma<DROP, RAG><<<grid, dim3(256), KV_LDS_BYTES, s>>>((const bf16*)a.qkv, (const bf16*)a.dctx, a.lse, a.delta,
+                                                                      (bf16*)a.dqkv, a.attn_mask, a.S, a.nh, scale,
+                                                                      a.mask_bias, a.drop);
   return hipGetLastError();
 }
 hipError_t attention_bwd_mfma(const AttnBwdDesc& a, hipStream_t s) {
   if (!attention_mfma_supported(a.S, a.dh)) return hipErrorInvalidValue;
-  // dropout is a compile-time variant so that the plain kernels carry none of its registers
-  return a.drop.thr ? attention_bwd_mfma_t<true>(a, s) : attention_bwd_mfma_t<false>(a, s);
+  if (a.S % TILE) return a.drop.thr ? attention_bwd_mfma_t<true, true>(a, s) : attention_bwd_mfma_t<false, true>(a, s);
+  return a.drop.thr ? attention_bwd_mfma_t<true, false>(a, s) : attention_bwd_mfma_t<false, false>(a, s);
 }
 
 }  // namespace mslt

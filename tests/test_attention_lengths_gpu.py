@@ -1,0 +1,21 @@
+"""Attention in bf16 mode at sequence lengths around the tile edges of the matrix-core kernels (32-row blocks, 64-key
+halves, 128-row tiles): a whole stage step against the oracle, with ragged batches, with and without dropout (lengths
+that are no multiple of four make the dropout quads straddle rows)."""
+import pytest
+
+from paper_2011_13635_amd import synth
+from parity_util import assert_parity, run_case
+
+pytestmark = pytest.mark.gpu
+
+# The bound is the bf16 mode's own (2e-2 of each tensor's largest entry).  Batches hold 400 tokens and more, and at least
+# six sequences, since on fewer (4x203: query-bias gradient 2.9e-2, with scalar fp32 attention 2.88e-2) the handful of
+# roundings behind a small attention gradient scatters past that bound by itself.
+
+
+@pytest.mark.parametrize("B,S", [(90, 5), (26, 31), (13, 33), (8, 64), (8, 65), (6, 127), (6, 129), (12, 203), (8, 257), (6, 385)])
+@pytest.mark.parametrize("p", [0.0, 0.1])
+def test_lengths_around_tile_edges(B, S, p):
+    r = run_case(synth.tiny_shape(3), B, S, 1, 2, False, 1, ragged=True, seed=3, dropout=(p, 7, 2) if p else None)
+    print(B, S, p, assert_parity(r, 1, f"{B}x{S} dropout {p}"))
+    r["model"].close()
