@@ -203,6 +203,10 @@ struct AttnBwdDesc {
 };
 hipError_t attention_fwd_simple(int dtype, const AttnDesc& d, hipStream_t s);
 hipError_t attention_bwd_simple(int dtype, const AttnBwdDesc& d, hipStream_t s);
+// fp32 on the matrix cores (head width 64)
+bool attention_f32_supported(int dh);
+hipError_t attention_fwd_f32(const AttnDesc& d, hipStream_t s);
+hipError_t attention_bwd_f32(const AttnBwdDesc& d, hipStream_t s);
 bool attention_mfma_supported(int S, int dh);
 hipError_t attention_fwd_mfma(const AttnDesc& d, hipStream_t s);
 hipError_t attention_bwd_mfma(const AttnBwdDesc& d, hipStream_t s);

@@ -867,6 +867,8 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
     ProfScope ps(m, PC_ATTN_FWD, 4.0 * TS * S * H, 4.0 * TS * H * m->esz);
     if (m->dtype == 1 && attention_mfma_supported(S, m->dh))
       HIP_TRY(attention_fwd_mfma(a, s));
+    else if (m->dtype == 0 && attention_f32_supported(m->dh))
+      HIP_TRY(attention_fwd_f32(a, s));
     else
       HIP_TRY(attention_fwd_simple(m->dtype, a, s));
   }
@@ -1041,6 +1043,8 @@ static int layer_backward_lower(mslt_model* m, int l, const mslt_batch* bt, int 
     ProfScope ps(m, PC_ATTN_BWD, 10.0 * TS * bt->seq * H, 8.0 * TS * H * m->esz);
     if (m->dtype == 1 && attention_mfma_supported(bt->seq, m->dh))
       HIP_TRY(attention_bwd_mfma(a, s));
+    else if (m->dtype == 0 && attention_f32_supported(m->dh))
+      HIP_TRY(attention_bwd_f32(a, s));
     else
       HIP_TRY(attention_bwd_simple(m->dtype, a, s));
     if (Tr > T)  // padded token rows must contribute nothing to the weight gradients

@@ -19,3 +19,12 @@ def test_lengths_around_tile_edges(B, S, p):
     r = run_case(synth.tiny_shape(3), B, S, 1, 2, False, 1, ragged=True, seed=3, dropout=(p, 7, 2) if p else None)
     print(B, S, p, assert_parity(r, 1, f"{B}x{S} dropout {p}"))
     r["model"].close()
+
+
+@pytest.mark.parametrize("B,S", [(3, 5), (4, 31), (4, 33), (3, 129), (2, 161)])
+@pytest.mark.parametrize("p", [0.0, 0.1])
+def test_fp32_lengths_around_block_edges(B, S, p):
+    """fp32 mode's matrix-core kernels: blocks of 32 rows, four of them shared by a workgroup's wavefronts."""
+    r = run_case(synth.tiny_shape(3), B, S, 1, 2, False, 0, ragged=True, seed=3, dropout=(p, 7, 2) if p else None)
+    assert_parity(r, 0, f"fp32 {B}x{S} dropout {p}")
+    r["model"].close()
