@@ -241,7 +241,8 @@ int mslt_profile_read(mslt_model* m, mslt_profile_entry* out, int cap, int* n);
  * kernel 0: guarded kernel (any shape).  kernel 1: 128-wide MFMA kernel, tile_m 0 (chosen by
  * shape), 128 or 256; M % 128 == 0, N % 128 == 0, K % 64 == 0.  kernel 2: large-tile kernel fed by
  * direct global-to-LDS loads, tile_m x tile_n one of 256x256, 256x128, 128x256, 128x128, ring stage
- * tile_k 64 (or 32, not for 128x128); M % tile_m == 0, N % tile_n == 0, K % tile_k == 0.  splitk > 1
+ * tile_k 64 (or 32, not for 128x128); M % tile_m == 0, N % tile_n == 0, K % tile_k == 0.  kernel 3:
+ * few-tile kernel, a_kcontig != 0, sizes as kernel 1, tile_m = tile_n = 32 or 64.  splitk > 1
  * (kernels 1 and 2) splits the contraction over workgroups and needs `partials`, DEVICE scratch of at
  * least splitk*M*N*4 bytes (partial_bytes says how large it is).  Returns MSLT_ERR_ARG for a shape or
  * choice the kernel does not take; nothing is enqueued then.  Does not block. */

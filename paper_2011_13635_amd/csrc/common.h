@@ -173,6 +173,12 @@ hipError_t gemm_ring_grouped_tn(const GemmDesc* d, int n, int tile_m, int tile_n
 hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int splitk, float* partials, hipStream_t s,
                      bool keep_partials = false);
 
+// Kernel for products with few output tiles (bf16, A k-contiguous; sizes as gemm_mfma_supported): tile x tile output
+// tiles, 32 or 64, the contraction split among the wavefronts of a workgroup.
+bool gemm_few_supported(const GemmDesc& d);
+int gemm_few_tile(const GemmDesc& d);   // tile it should take a product with, 0: another kernel should
+hipError_t gemm_few(const GemmDesc& d, int tile, hipStream_t s);
+
 // ---- attention ------------------------------------------------------------------------------
 struct AttnDesc {
   const void* qkv;    // [T, 3H] rows = tokens: Q | K | V, head h at columns h*dh

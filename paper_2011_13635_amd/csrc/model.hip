@@ -738,10 +738,14 @@ static int run_gemm(mslt_model* m, const GemmDesc& d, bool allow_splitk = false,
   // to its 128x128 form, two workgroups per compute unit, fed by direct loads and transposing LDS reads;
   // data-gradient products stay on the 128-wide register-staged kernel, except the one with a wide output (the
   // gradient of the feed-forward layer's hidden activation), which gains on the large tiles in the step as well.
+  // A product with too few tiles for either goes to the kernel that splits the contraction inside a workgroup.
   RingPlan rp;
+  const int few = use_mfma ? gemm_few_tile(d) : 0;
   const bool nt = d.a_kcontig && d.b_kcontig, tn = !d.a_kcontig && !d.b_kcontig;
   const bool nn_wide = d.a_kcontig && !d.b_kcontig && d.N >= 2048 && d.M >= 4096;
-  if (use_mfma && tn && gemm_ring_supported(d, 128, 128, 64)) {
+  if (few) {
+    HIP_TRY(gemm_few(d, few, st));
+  } else if (use_mfma && tn && gemm_ring_supported(d, 128, 128, 64)) {
     int sk = allow_splitk ? pick_splitk(d.M, d.N, d.K) : 1;
     float* kept = nullptr;
     if (sk > 1 && sum_later && d.epi.out_f32 && d.epi.ldo == d.N && !d.epi.bias && d.epi.act == EPI_NONE && !d.epi.drop.thr &&
@@ -1491,8 +1495,13 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
       return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d not taken by the large-tile kernel with tile %dx%dx%d, splitk %d", M, N,
                   K, tile_m, tile_n, tile_k, splitk);
     HIP_TRY(gemm_ring(d, tile_m, tile_n, tile_k, splitk, (float*)partials, st));
+  } else if (kernel == 3) {
+    if (!gemm_few_supported(d) || tile_m != tile_n || (tile_m != 32 && tile_m != 64) || splitk != 1)
+      return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d not taken by the few-tile kernel with tile %dx%d, splitk %d", M, N, K,
+                  tile_m, tile_n, splitk);
+    HIP_TRY(gemm_few(d, tile_m, st));
   } else {
-    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0, 1 or 2");
+    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 3");
   }
   return MSLT_OK;
 }

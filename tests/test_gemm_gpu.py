@@ -73,6 +73,19 @@ def test_guarded_kernel_at_tile_edges(M, N, K, akc, bkc):
     assert np.array_equal(c.cpu().numpy().astype(np.float64), ref)
 
 
+@pytest.mark.parametrize("M,N,K", [(128, 128, 64), (128, 768, 128), (384, 256, 576), (256, 384, 3136)])
+@pytest.mark.parametrize("tile", [32, 64])
+@pytest.mark.parametrize("bkc", [1, 0])
+def test_few_tile_kernel_equals_plain_definition(M, N, K, tile, bkc):
+    # fewer k groups of 64 than wavefronts, one more than a multiple of them, and many; exact in fp32 as above
+    import torch
+    ta, tb, ref = _operands(torch, M, N, K, 1, bkc, seed=40 + bkc)
+    c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda:0")
+    binding.mslt_debug_gemm(ta, tb, c, M, N, K, 1, bkc, 3, tile, tile, 64, 1, None)
+    torch.cuda.synchronize()
+    assert np.array_equal(c.cpu().numpy().astype(np.float64), ref)
+
+
 def test_unsupported_choices_are_refused_without_work():
     import torch
     ta, tb, _ = _operands(torch, 256, 256, 128, 1, 1, seed=3)
