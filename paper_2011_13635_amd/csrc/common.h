@@ -176,7 +176,9 @@ hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int spli
 // Kernel for products with few output tiles (bf16, A k-contiguous; sizes as gemm_mfma_supported): tile x tile output
 // tiles, 32 or 64, the contraction split among the wavefronts of a workgroup.
 bool gemm_few_supported(const GemmDesc& d);
-int gemm_few_tile(const GemmDesc& d);   // tile it should take a product with, 0: another kernel should
+// Tile it should take a product with, 0: another kernel should.  rows: d.M, or the rows of the part of a product that
+// has to be computed as that part alone would be (its order of additions is not the other kernels').
+int gemm_few_tile(const GemmDesc& d, int rows);
 hipError_t gemm_few(const GemmDesc& d, int tile, hipStream_t s);
 
 // ---- attention ------------------------------------------------------------------------------

@@ -7,9 +7,9 @@
 // partial tiles are added in order of w in LDS before the shared epilogue.  So a long contraction is a short chain in
 // every wavefront, with no second launch and no partial sums in memory.  A k group of a row is one 128-byte cache line,
 // loaded by eight lanes (fragments loaded straight into registers, half a line per row, took 13.3 instead of 8.4 us at
-// 128x768x3072: the vector memory path is what bounds this kernel); D groups are in flight per wavefront in registers.  They pass through
-// a patch of LDS that only their own wavefront uses, so there is no barrier in the k loop: k-contiguous operands as
-// [rows][64 k] with the 16-byte chunks XOR-swizzled by the row, a k-strided B (the weight in dX = dY W) as [64 k][TN],
+// 128x768x3072: the vector memory path is what bounds this kernel); D groups are in flight per wavefront in registers.
+// They pass through a patch of LDS that only their own wavefront uses, so there is no barrier in the k loop:
+// k-contiguous operands as [rows][64 k] with the 16-byte chunks XOR-swizzled by the row, a k-strided B (the weight in dX = dY W) as [64 k][TN],
 // read back through the transposing read (sixteen lanes that fetch four consecutive n of four k receive four
 // consecutive k of one n).
 // The product is formed transposed (n in the accumulator's row index), so a lane holds four consecutive columns.
@@ -194,9 +194,9 @@ bool gemm_few_supported(const GemmDesc& d) { return d.a_kcontig && gemm_mfma_sup
 // Two 64-wide workgroups on a compute unit with one group in flight beat one with two in flight: 512x3072x768 9.0
 // against 13.7.  A long contraction is better split over workgroups: at 512x768x30592 the 64-wide form took 154, a
 // split by 8 of the 128-wide kernel 53.
-int gemm_few_tile(const GemmDesc& d) {
+int gemm_few_tile(const GemmDesc& d, int rows) {
   if (!gemm_few_supported(d)) return 0;
-  const long long tiles = (long long)(d.M / 64) * (d.N / 64);
+  const long long tiles = (long long)((rows + 63) / 64) * (d.N / 64);
   if (4 * tiles <= 256 && d.K <= 8192) return 32;
   if (tiles <= 512 && d.K <= 4096) return 64;
   return 0;

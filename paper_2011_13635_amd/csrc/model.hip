@@ -160,6 +160,7 @@ struct mslt_model {
   // pinned host scalars
   int32_t* h_counters; float* h_loss;
   // last step
+  int few_div = 1;         // 2 while the forward of a step that belongs on two chains is queued as one (see `halves`)
   bool have_grads;
   int last_f, last_k, last_emb, last_B, last_S, last_M;
   const void* last_prefix;
@@ -740,7 +741,7 @@ static int run_gemm(mslt_model* m, const GemmDesc& d, bool allow_splitk = false,
   // gradient of the feed-forward layer's hidden activation), which gains on the large tiles in the step as well.
   // A product with too few tiles for either goes to the kernel that splits the contraction inside a workgroup.
   RingPlan rp;
-  const int few = use_mfma ? gemm_few_tile(d) : 0;
+  const int few = use_mfma ? gemm_few_tile(d, d.M / m->few_div) : 0;
   const bool nt = d.a_kcontig && d.b_kcontig, tn = !d.a_kcontig && !d.b_kcontig;
   const bool nn_wide = d.a_kcontig && !d.b_kcontig && d.N >= 2048 && d.M >= 4096;
   if (few) {
@@ -1125,6 +1126,7 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   m->later.clear();          // (a step that failed half-way may have left jobs behind)
   m->later_used = 0;
   m->later_on = m->lpg == 1;
+  m->few_div = 1;
 
   // S0: batch check and compaction of the predicted positions (only index scratch is written)
   HIP_TRY(batch_scan(bt->input_ids, bt->token_type_ids, bt->attn_mask, bt->labels, T, m->V, m->cfg.type_vocab, m->cap,
@@ -1152,7 +1154,10 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   // of the step; four chains on four streams were slower.  Dropout indexes its decisions by position
   // in the whole batch: the second half's kernels get keys that carry its offset (S even keeps the
   // offset of the attention probabilities a multiple of 4).  Off while event profiling.
-  const bool halves = !m->prof.on && m->dtype == 1 && m->mfma && B % 2 == 0 && (T / 2) % 128 == 0 && Tr == T && S % 2 == 0;
+  // (queued as one chain then, with the kernels the halves would take, so that the results are the same bits)
+  const bool two_chains = m->dtype == 1 && m->mfma && B % 2 == 0 && (T / 2) % 128 == 0 && Tr == T && S % 2 == 0;
+  const bool halves = two_chains && !m->prof.on;
+  m->few_div = two_chains && !halves ? 2 : 1;
   const FwdPart parts[2] = {{0, B / 2, s}, {B / 2, B / 2, m->side}};
   if (halves) {
     HIP_TRY(hipEventRecord(m->ev_fork, s));
@@ -1178,6 +1183,7 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
     x = m->stash[l - f].xout;
   }
   if (halves) RC(side_join(m));
+  m->few_div = 1;
   HIP_TRY(hipEventSynchronize(m->ev_scan));
   // M: compacted rows (predicted positions, plus every first token when there is a next-sentence head);
   // Mn: those of them that carry a masked-LM label
