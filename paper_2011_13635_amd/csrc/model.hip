@@ -1155,7 +1155,11 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   // in the whole batch: the second half's kernels get keys that carry its offset (S even keeps the
   // offset of the attention probabilities a multiple of 4).  Off while event profiling.
   // (queued as one chain then, with the kernels the halves would take, so that the results are the same bits)
-  const bool two_chains = m->dtype == 1 && m->mfma && B % 2 == 0 && (T / 2) % 128 == 0 && Tr == T && S % 2 == 0;
+  // One chain where the widest product has at most 2^30 operations: such a product lasts about as long as its launch,
+  // and a second chain only doubles the launches the host has to queue.  Two chains / one, us: 128-wide 2+1 layer model
+  // 4x64 408 / 313, 32x64 446 / 342, 64x128 (2^30) 461 / 445; BERT-Base 2x128 (1.1 * 2^30) 1192 / 1234.
+  const bool two_chains = m->dtype == 1 && m->mfma && B % 2 == 0 && (T / 2) % 128 == 0 && Tr == T && S % 2 == 0 &&
+                          (double)T * m->F * H > (double)(1 << 29);
   const bool halves = two_chains && !m->prof.on;
   m->few_div = two_chains && !halves ? 2 : 1;
   const FwdPart parts[2] = {{0, B / 2, s}, {B / 2, B / 2, m->side}};
