@@ -250,6 +250,18 @@ int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, void* C, int
                     int b_kcontig, int out_f32, int kernel, int tile_m, int tile_n, int tile_k, int splitk,
                     void* partials, size_t partial_bytes);
 
+/* Test aid for the attention of one layer (Section 4.1, the architecture of BERT) through the kernels a step takes for
+ * these sizes, forward and, when dctx is not null, backward, on DEVICE operands, enqueued on hip_stream.  precision as
+ * in mslt_config: 0 fp32, 1 bf16 (qkv, ctx, dctx, dqkv).  qkv [batch*seq, 3H]: Q | K | V, head h at columns
+ * h*head_width, H = n_heads*head_width <= 2048; ctx, dctx [batch*seq, H]; ctx_f32 [batch*seq, H] or null: ctx once more,
+ * unrounded (the backward then takes it, as in a step); lse, delta [batch, n_heads, seq] fp32; dqkv as qkv.  All
+ * operands 16-byte aligned.  attn_mask [batch, seq] and mask_bias as in a step, with at least one 1 per sequence.
+ * dropout > 0: keep decisions of mslt_set_dropout for (seed, step 0, layer 0, site 1).  Returns MSLT_ERR_ARG for sizes
+ * no model can have; nothing is enqueued then.  Does not block. */
+int mslt_debug_attention(void* hip_stream, int precision, int batch, int seq, int n_heads, int head_width, const void* qkv,
+                         const int32_t* attn_mask, float mask_bias, float dropout, uint64_t seed, void* ctx, float* ctx_f32,
+                         float* lse, const void* dctx, float* delta, void* dqkv);
+
 /* Waits until all work enqueued on the model's stream has finished. */
 int mslt_sync(const mslt_model* m);
 

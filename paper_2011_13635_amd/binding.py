@@ -20,6 +20,7 @@ EXPORTS = [
     "mslt_set_dropout", "mslt_debug_masked",
     "mslt_debug_prefix_output", "mslt_grow", "mslt_sync", "mslt_destroy", "mslt_last_error",
     "mslt_profile_enable", "mslt_profile_read", "mslt_debug_gemm",
+    "mslt_debug_attention",
 ]
 
 MSLT_OK, MSLT_ERR_ARG, MSLT_ERR_STATE, MSLT_ERR_DATA, MSLT_ERR_HIP, MSLT_ERR_NONFINITE = 0, -1, -2, -3, -4, -5
@@ -91,6 +92,7 @@ def load_library():
     lib.mslt_profile_read.argtypes = [vp, P(ProfileEntry), C.c_int, P(C.c_int)]
     lib.mslt_sync.argtypes = [vp]
     lib.mslt_debug_gemm.argtypes = [vp, vp, vp, vp] + [C.c_int] * 11 + [vp, sz]
+    lib.mslt_debug_attention.argtypes = [vp] + [C.c_int] * 5 + [vp, vp, C.c_float, C.c_float, C.c_uint64] + [vp] * 6
     lib.mslt_destroy.argtypes = [vp]
     lib.mslt_last_error.argtypes = []
     lib.mslt_last_error.restype = C.c_char_p
@@ -140,6 +142,30 @@ def mslt_debug_gemm(a, b, c, M, N, K, a_kcontig, b_kcontig, kernel, tile_m=0, ti
                                           C.c_void_p(c.data_ptr()), M, N, K, int(a_kcontig), int(b_kcontig), out_f32, kernel,
                                           tile_m, tile_n, tile_k, splitk,
                                           C.c_void_p(partials.data_ptr()) if partials is not None else None, pb))
+
+
+def mslt_debug_attention(qkv, attn_mask, n_heads, head_width, mask_bias=-10000.0, dropout=0.0, seed=0, dctx=None, stream=None):
+    """Attention of one layer, forward and (with dctx) backward, through the kernels a step takes.  qkv: device tensor
+    [B, S, 3H], fp32 or bf16; attn_mask: int32 [B, S]; dctx: [B, S, H] of qkv's type.  Returns a dict of device tensors:
+    ctx, ctx_f32, lse and, with dctx, dqkv.  Enqueues only."""
+    import torch
+    B, S, _ = qkv.shape
+    H = n_heads * head_width
+    st = stream if stream is not None else torch.cuda.current_stream(qkv.device)
+    new = lambda *shape, dtype: torch.full(shape, float("nan"), dtype=dtype, device=qkv.device)
+    out = {"ctx": new(B, S, H, dtype=qkv.dtype), "ctx_f32": new(B, S, H, dtype=torch.float32),
+           "lse": new(B, n_heads, S, dtype=torch.float32)}
+    delta = None
+    if dctx is not None:
+        out["dqkv"] = new(B, S, 3 * H, dtype=qkv.dtype)
+        delta = new(B, n_heads, S, dtype=torch.float32)
+    ptr = lambda t: C.c_void_p(t.data_ptr()) if t is not None else None
+    _check(load_library().mslt_debug_attention(C.c_void_p(st.cuda_stream), int(qkv.dtype == torch.bfloat16), B, S, n_heads,
+                                               head_width, ptr(qkv), ptr(attn_mask), mask_bias, dropout, seed, ptr(out["ctx"]),
+                                               ptr(out["ctx_f32"]), ptr(out["lse"]), ptr(dctx), ptr(delta),
+                                               ptr(out.get("dqkv"))))
+    out["delta"] = delta      # (kept alive with the rest while the kernels are queued)
+    return out
 
 
 class Model:

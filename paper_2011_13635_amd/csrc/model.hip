@@ -837,6 +837,18 @@ static int ln_forward(mslt_model* m, const void* a, const void* r, const float* 
   return MSLT_OK;
 }
 
+// ---- attention dispatch ---------------------------------------------------------------------
+static hipError_t attention_fwd(int dtype, const AttnDesc& a, hipStream_t s) {
+  if (dtype == 1 && attention_mfma_supported(a.S, a.dh)) return attention_fwd_mfma(a, s);
+  if (dtype == 0 && attention_f32_supported(a.dh)) return attention_fwd_f32(a, s);
+  return attention_fwd_simple(dtype, a, s);
+}
+static hipError_t attention_bwd(int dtype, const AttnBwdDesc& a, hipStream_t s) {
+  if (dtype == 1 && attention_mfma_supported(a.S, a.dh)) return attention_bwd_mfma(a, s);
+  if (dtype == 0 && attention_f32_supported(a.dh)) return attention_bwd_f32(a, s);
+  return attention_bwd_simple(dtype, a, s);
+}
+
 // ---- one encoder layer ----------------------------------------------------------------------
 // Every kernel of the forward pass works on token rows (or whole sequences) independently of the
 // other rows, so a layer can run on a range of the batch's sequences: FwdPart names the range and
@@ -870,12 +882,7 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
   {
     const double TS = (double)nb * S;
     ProfScope ps(m, PC_ATTN_FWD, 4.0 * TS * S * H, 4.0 * TS * H * m->esz);
-    if (m->dtype == 1 && attention_mfma_supported(S, m->dh))
-      HIP_TRY(attention_fwd_mfma(a, s));
-    else if (m->dtype == 0 && attention_f32_supported(m->dh))
-      HIP_TRY(attention_fwd_f32(a, s));
-    else
-      HIP_TRY(attention_fwd_simple(m->dtype, a, s));
+    HIP_TRY(attention_fwd(m->dtype, a, s));
   }
   RC(linear_fwd(m, ctx, rows, H, Wg(m, t_app(m, l, L_WO)), H, Wf(m, t_app(m, l, L_BO)), y, 0, H, EPI_NONE, nullptr,
                 dspec(m, l, SITE_ATTN_OUT, r0 * H), s));
@@ -1046,12 +1053,7 @@ static int layer_backward_lower(mslt_model* m, int l, const mslt_batch* bt, int 
   {
     const double TS = (double)bt->batch * bt->seq;
     ProfScope ps(m, PC_ATTN_BWD, 10.0 * TS * bt->seq * H, 8.0 * TS * H * m->esz);
-    if (m->dtype == 1 && attention_mfma_supported(bt->seq, m->dh))
-      HIP_TRY(attention_bwd_mfma(a, s));
-    else if (m->dtype == 0 && attention_f32_supported(m->dh))
-      HIP_TRY(attention_bwd_f32(a, s));
-    else
-      HIP_TRY(attention_bwd_simple(m->dtype, a, s));
+    HIP_TRY(attention_bwd(m->dtype, a, s));
     if (Tr > T)  // padded token rows must contribute nothing to the weight gradients
       HIP_TRY(fill_zero((char*)m->d_qkv + (size_t)T * 3 * H * m->esz, (size_t)(Tr - T) * 3 * H * m->esz, s));
   }
@@ -1513,6 +1515,31 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
   } else {
     return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 3");
   }
+  return MSLT_OK;
+}
+
+extern "C" int mslt_debug_attention(void* hip_stream, int precision, int batch, int seq, int n_heads, int head_width,
+                                    const void* qkv, const int32_t* attn_mask, float mask_bias, float dropout, uint64_t seed,
+                                    void* ctx, float* ctx_f32, float* lse, const void* dctx, float* delta, void* dqkv) {
+  if (!qkv || !attn_mask || !ctx || !lse) return fail(MSLT_ERR_ARG, "debug_attention: null operand");
+  if (dctx && (!delta || !dqkv)) return fail(MSLT_ERR_ARG, "debug_attention: the backward needs delta and dqkv");
+  if (precision != 0 && precision != 1) return fail(MSLT_ERR_ARG, "debug_attention: precision must be 0 or 1");
+  if (batch < 1 || seq < 1 || n_heads < 1 || head_width < 1 || head_width > 128 || (long long)n_heads * head_width > 2048 ||
+      n_heads * head_width % 4 || (long long)batch * seq > (1 << 22))
+    return fail(MSLT_ERR_ARG, "debug_attention: size outside what a model takes");
+  if (!(dropout >= 0.f && dropout < 1.f)) return fail(MSLT_ERR_ARG, "debug_attention: dropout outside [0, 1)");
+  hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
+  DropSpec drop;
+  if (dropout > 0.f) {
+    drop.key = drop_key(seed, 0, 0, SITE_ATTN_PROBS);
+    drop.thr = (uint32_t)lrintf(dropout * 65536.0f);
+    drop.scale = 1.0f / (1.0f - dropout);
+  }
+  const AttnDesc f{qkv, ctx, lse, attn_mask, batch, seq, n_heads, head_width, mask_bias, drop, ctx_f32};
+  HIP_TRY(attention_fwd(precision, f, st));
+  if (!dctx) return MSLT_OK;
+  const AttnBwdDesc b{qkv, ctx, dctx, lse, delta, dqkv, attn_mask, batch, seq, n_heads, head_width, mask_bias, drop, ctx_f32};
+  HIP_TRY(attention_bwd(precision, b, st));
   return MSLT_OK;
 }
 

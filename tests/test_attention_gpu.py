@@ -1,0 +1,94 @@
+"""The attention kernels alone, through the C ABI (mslt_debug_attention), against the plain definition in float64 on
+the same operands: lengths around the edges of blocks and tiles, ragged key masks, dropout, both precisions, head
+widths of the matrix-core and of the wave-per-row kernels, batches whose forward workgroups walk several work items.
+
+Bounds.  Where probabilities and their gradients are kept in fp32 (fp32 mode at any length, bf16 mode at lengths that
+are no multiple of 128) an output is off by the fp32 errors of its terms: a probability carries that of a 64-term dot
+product and of one exponential, about 2^-20 of itself, so 2^-16 of the sum of the terms' magnitudes holds with room.
+Results stored in bf16 (seven mantissa bits) add half a unit in the last place, at most 2^-8 of the value."""
+import numpy as np
+import pytest
+
+from oracle import mslt_oracle as O
+from paper_2011_13635_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _values(torch, shape, seed, scale=1.0, shift=None):
+    """Normal values exactly representable in bf16, float64 on the host."""
+    g = torch.Generator()
+    g.manual_seed(seed)
+    x = torch.randn(shape, generator=g, dtype=torch.float64) * scale
+    if shift is not None:
+        x = x + shift
+    return x.to(torch.bfloat16).to(torch.float64)
+
+
+def _reference(qkv, mask, nh, dh, bias, dc, mA):
+    """Outputs and the sums of the magnitudes of their terms, by the definition, in float64."""
+    B, S, _ = qkv.shape
+    H = nh * dh
+    q, k, v = (qkv[..., i * H:(i + 1) * H].reshape(B, S, nh, dh).transpose(0, 2, 1, 3) for i in range(3))
+    g = dc.reshape(B, S, nh, dh).transpose(0, 2, 1, 3)
+    sc = 1.0 / np.sqrt(dh)
+    a = q @ k.transpose(0, 1, 3, 2) * sc + np.where(mask, 0.0, bias)[:, None, None, :]
+    mx = a.max(-1, keepdims=True)
+    e = np.exp(a - mx)
+    den = e.sum(-1, keepdims=True)
+    p = e / den
+    pd = p * mA
+    dp = (g @ v.transpose(0, 1, 3, 2)) * mA
+    delta = (p * dp).sum(-1, keepdims=True)
+    ds = p * (dp - delta)
+    ms = p * (np.abs(dp) + np.abs(delta))
+    T = lambda x: x.transpose(0, 1, 3, 2)
+    back = lambda x: x.transpose(0, 2, 1, 3).reshape(B, S, H)
+    out = {"ctx": back(pd @ v), "dq": back(ds @ k) * sc, "dk": back(T(ds) @ q) * sc, "dv": back(T(pd) @ g)}
+    mag = {"ctx": back(pd @ np.abs(v)), "dq": back(ms @ np.abs(k)) * sc, "dk": back(T(ms) @ np.abs(q)) * sc,
+           "dv": back(T(pd) @ np.abs(g))}
+    return out, mag, (mx + np.log(den))[..., 0]
+
+
+def _run(B, S, nh, dh, precision, p, seed, mask=None, bias=-10000.0, ref_bias=None):
+    import torch
+    H = nh * dh
+    common = _values(torch, (1, 1, 3 * H), seed + 1)          # a common part of the keys: rows of dS have to sum to zero
+    qkv = _values(torch, (B, S, 3 * H), seed, 1.0, common)
+    dc = _values(torch, (B, S, H), seed + 2)
+    if mask is None:
+        n = S // 2 + (synth.rand_u64(seed, 5, np.arange(B)) % (S - S // 2 + 1)).astype(np.int64)
+        mask = np.arange(S)[None, :] < np.maximum(n, 1)[:, None]
+    dt = torch.bfloat16 if precision else torch.float32
+    got = binding.mslt_debug_attention(qkv.to(dt).cuda(), torch.tensor(mask.astype(np.int32)).cuda(), nh, dh, bias, p, seed,
+                                       dc.to(dt).cuda())
+    torch.cuda.synchronize()
+    got = {k: t.to(torch.float64).cpu().numpy() for k, t in got.items()}
+    mA = O.Dropout(p, seed, 0).mask(0, O.SITE_ATTN_PROBS, (B, nh, S, S)) if p else 1.0
+    ref, mag, lse = _reference(qkv.numpy(), mask, nh, dh, bias if ref_bias is None else ref_bias, dc.numpy(), mA)
+    for i, n in enumerate(("dq", "dk", "dv")):
+        got[n] = got["dqkv"][..., i * H:(i + 1) * H]
+    return got, ref, mag, lse
+
+
+def _check(got, ref, mag, lse, precision, label):
+    assert np.abs(got["lse"] - lse).max() <= 2.0 ** -18 * max(np.abs(lse).max(), 1.0), label
+    worst = {}
+    for n, r in ref.items():
+        x = got["ctx_f32"] if n == "ctx" else got[n]
+        rounding = 2.0 ** -8 * np.abs(r) if precision and n != "ctx" else 0.0
+        over = (np.abs(x - r) - rounding) / (mag[n] + 1e-30)
+        assert np.isfinite(over).all(), (label, n)
+        worst[n] = over.max()
+    print(label, {n: f"2^{np.log2(max(w, 1e-30)):.1f}" for n, w in worst.items()}, flush=True)
+    for n, w in worst.items():
+        assert w <= 2.0 ** -16, (label, n, w)
+    if precision:
+        assert (np.abs(got["ctx"] - got["ctx_f32"]) <= 2.0 ** -8 * np.abs(got["ctx_f32"])).all(), label
+
+
+@pytest.mark.parametrize("S", [1, 31, 33, 128, 161, 257])
+@pytest.mark.parametrize("p", [0.0, 0.1])
+@pytest.mark.parametrize("precision,dh", [(0, 64), (0, 32), (1, 32)])
+def test_fp32_mode_and_other_head_widths(S, p, precision, dh):
+    _check(*_run(2, S, 2, dh, precision, p, seed=300 + S), precision, f"precision {precision} dh={dh} S={S} p={p}")
