@@ -66,7 +66,7 @@ typedef struct {
   int max_predictions; /* largest number of predicted positions per step; 0 = max_batch*max_seq */
   int precision;       /* 0 fp32, 1 bf16 compute with fp32 master */
   float ln_eps;        /* LayerNorm epsilon (1e-12) */
-  float mask_bias;     /* added to the scores of padded keys (-10000) */
+  float mask_bias;     /* added to the scores of padded keys (-10000); may be as low as the type goes, or -infinity */
   int layers_per_group; /* 0 or 1: every layer has its own parameters (BERT).  n > 1: the grouped ALBERT
                           variant of Section 3.3 - each run of n consecutive layers shares one parameter set
                           ("layer g" in the tensor table is the set of group g; there are n_layers_max / n sets),
@@ -86,7 +86,8 @@ typedef struct {
 
 /* One masked-LM batch.  DEVICE pointers to int32 arrays of batch*seq entries, row-major
  * [batch][seq], owned by the caller and valid until the step's stream work has finished.
- * attn_mask: 1 token, 0 padding.  labels: original id at predicted positions, -100 elsewhere. */
+ * attn_mask: 1 token, 0 padding; in a sequence of padding alone (one that fills up a batch) the bias is the same for
+ * all keys and cancels.  labels: original id at predicted positions, -100 elsewhere. */
 typedef struct {
   const int32_t* input_ids;
   const int32_t* token_type_ids;

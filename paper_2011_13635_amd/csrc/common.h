@@ -182,13 +182,17 @@ int gemm_few_tile(const GemmDesc& d, int rows);
 hipError_t gemm_few(const GemmDesc& d, int tile, hipStream_t s);
 
 // ---- attention ------------------------------------------------------------------------------
+// The mask bias as the kernels get it.  Next to an open key a masked one has probability zero for any bias this low, and
+// -1e30 leaves room for the factors and sums a kernel puts it through: the type's lowest value or -infinity would
+// overflow there, and a block of nothing but -infinity has no maximum a softmax could be taken against.
+inline float attention_bias(float mask_bias) { return mask_bias < -1e30f ? -1e30f : mask_bias; }
 struct AttnDesc {
   const void* qkv;    // [T, 3H] rows = tokens: Q | K | V, head h at columns h*dh
   void* ctx;          // [T, H]
   float* lse;         // [B, nh, S] natural log-sum-exp of the masked scaled scores, or null
-  const int32_t* attn_mask;  // [B, S]
+  const int32_t* attn_mask;  // [B, S], at least one open key per sequence
   int B, S, nh, dh;
-  float mask_bias;
+  float mask_bias;    // finite, see attention_bias
   DropSpec drop;      // dropout of the attention probabilities; element index ((b*nh + h)*S + q)*S + key
   float* ctx_f32 = nullptr;   // optional second copy of ctx in fp32, unrounded, for the backward pass (see AttnBwdDesc)
 };
@@ -227,10 +231,11 @@ hipError_t widen_to_f32(int dtype, const void* src, float* dst, size_t n, hipStr
 // checks the batch and compacts predicted positions.  counters[0] = M, counters[1] = error bits
 // (1 id range, 2 type range, 4 label range, 8 mask value).  inv[t] = j if t is the j-th predicted
 // position else -1.
-// pos/lab hold at most `cap` entries; counters[0] still reports the true count.
+// pos/lab hold at most `cap` entries; counters[0] still reports the true count.  key_mask [T]: attn_mask for sequences
+// with at least one open key, all ones for the others (T is a multiple of n_seq).
 hipError_t batch_scan(const int32_t* ids, const int32_t* tt, const int32_t* am, const int32_t* labels, int T, int vocab,
                       int type_vocab, int cap, int32_t* pos, int32_t* lab, int32_t* inv, int32_t* counters,
-                      int cls_every, const int32_t* nsp_labels, int n_seq, hipStream_t s);
+                      int cls_every, const int32_t* nsp_labels, int n_seq, int32_t* key_mask, hipStream_t s);
 
 struct LnStash {
   void* xhat = nullptr;   // [rows, H] activation type, or null

@@ -116,7 +116,7 @@ struct mslt_model {
   bool wide;
   float *d_d32, *d_z1_32;
   float *delta;
-  int32_t *pos, *lab, *inv, *counters;
+  int32_t *pos, *lab, *inv, *counters, *key_mask;   // key_mask: see batch_scan
   void *xm, *ut, *gt, *xhat_t, *hm, *dz, *d_hm, *d_gt, *d_ut, *d_xm;
   void *c_g, *c_u, *c_du;              // compacted FFN rows of the top layer [Mp, F]
   float *rstd_t, *logits, *row_loss, *lse_t, *loss;
@@ -339,7 +339,7 @@ static size_t carve(mslt_model* m, char* base) {
   m->d_z0 = b.take<void>(TH);
   m->delta = b.take<float>(lse_bytes);
   m->pos = b.take<int32_t>((size_t)m->cap * 4); m->lab = b.take<int32_t>((size_t)m->cap * 4);
-  m->inv = b.take<int32_t>(Tp * 4); m->counters = b.take<int32_t>(64);
+  m->inv = b.take<int32_t>(Tp * 4); m->key_mask = b.take<int32_t>(Tp * 4); m->counters = b.take<int32_t>(64);
   m->xm = b.take<void>(MH); m->ut = b.take<void>(MH); m->gt = b.take<void>(MH); m->xhat_t = b.take<void>(MH);
   m->hm = b.take<void>(MH); m->d_hm = b.take<void>(MH); m->d_gt = b.take<void>(MH);
   m->d_ut = b.take<void>(MH); m->d_xm = b.take<void>(MH);
@@ -877,8 +877,8 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
   void* xout = at(Xout, H * e);
   RC(linear_fwd(m, xin, rows, H, Wg(m, t_app(m, l, L_WQ)), 3 * H, Wf(m, t_app(m, l, L_BQ)), qkv, 0, 3 * H, EPI_NONE, nullptr,
                 DropSpec(), s));
-  AttnDesc a{qkv, ctx, st ? (float*)at(st->lse, (size_t)m->nh * 4) : nullptr, bt->attn_mask + r0, nb, S, m->nh, m->dh,
-             m->cfg.mask_bias, dspec(m, l, SITE_ATTN_PROBS, r0 * m->nh * S), st ? (float*)at(st->ctx32, H * 4) : nullptr};
+  AttnDesc a{qkv, ctx, st ? (float*)at(st->lse, (size_t)m->nh * 4) : nullptr, m->key_mask + r0, nb, S, m->nh, m->dh,
+             attention_bias(m->cfg.mask_bias), dspec(m, l, SITE_ATTN_PROBS, r0 * m->nh * S), st ? (float*)at(st->ctx32, H * 4) : nullptr};
   {
     const double TS = (double)nb * S;
     ProfScope ps(m, PC_ATTN_FWD, 4.0 * TS * S * H, 4.0 * TS * H * m->esz);
@@ -1048,8 +1048,8 @@ static int layer_backward_lower(mslt_model* m, int l, const mslt_batch* bt, int 
   const int H = m->H;
   const LayerStash& st = m->stash[l - m->stash_base];
   hipStream_t s = m->stream;
-  AttnBwdDesc a{st.qkv, st.ctx, m->d_c, st.lse, m->delta, m->d_qkv, bt->attn_mask, bt->batch, bt->seq, m->nh, m->dh,
-                m->cfg.mask_bias, dspec(m, l, SITE_ATTN_PROBS), st.ctx32};
+  AttnBwdDesc a{st.qkv, st.ctx, m->d_c, st.lse, m->delta, m->d_qkv, m->key_mask, bt->batch, bt->seq, m->nh, m->dh,
+                attention_bias(m->cfg.mask_bias), dspec(m, l, SITE_ATTN_PROBS), st.ctx32};
   {
     const double TS = (double)bt->batch * bt->seq;
     ProfScope ps(m, PC_ATTN_BWD, 10.0 * TS * bt->seq * H, 8.0 * TS * H * m->esz);
@@ -1132,7 +1132,7 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
 
   // S0: batch check and compaction of the predicted positions (only index scratch is written)
   HIP_TRY(batch_scan(bt->input_ids, bt->token_type_ids, bt->attn_mask, bt->labels, T, m->V, m->cfg.type_vocab, m->cap,
-                     m->pos, m->lab, m->inv, m->counters, m->nsp ? S : 0, m->nsp ? bt->nsp_labels : nullptr, B, s));
+                     m->pos, m->lab, m->inv, m->counters, m->nsp ? S : 0, m->nsp ? bt->nsp_labels : nullptr, B, m->key_mask, s));
   HIP_TRY(hipMemcpyAsync(m->h_counters, m->counters, 12, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipEventRecord(m->ev_scan, s));
   const int Tr = m->mfma ? (int)rup(T, 128) : T;
@@ -1535,6 +1535,7 @@ extern "C" int mslt_debug_attention(void* hip_stream, int precision, int batch, 
     drop.thr = (uint32_t)lrintf(dropout * 65536.0f);
     drop.scale = 1.0f / (1.0f - dropout);
   }
+  mask_bias = attention_bias(mask_bias);
   const AttnDesc f{qkv, ctx, lse, attn_mask, batch, seq, n_heads, head_width, mask_bias, drop, ctx_f32};
   HIP_TRY(attention_fwd(precision, f, st));
   if (!dctx) return MSLT_OK;

@@ -97,15 +97,29 @@ __global__ void __launch_bounds__(1024) k_batch_scan(const int32_t* __restrict__
                                                      const int32_t* __restrict__ am, const int32_t* __restrict__ labels,
                                                      int T, int vocab, int type_vocab, int cap, int32_t* pos,
                                                      int32_t* lab, int32_t* inv, int32_t* counters, int cls_every,
-                                                     const int32_t* __restrict__ nsp_labels, int n_seq) {
+                                                     const int32_t* __restrict__ nsp_labels, int n_seq, int seq,
+                                                     int32_t* __restrict__ key_mask) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (blockIdx.x > 0) {
+    // workgroups after the first: the key mask the attention reads, one sequence per wavefront.  Without an open key
+    // the bias of masked keys is the same for all keys of the sequence and cancels in the softmax, but a low one
+    // swallows the scores (and the log-sum-exp of the row) in fp32; so such a sequence counts as open throughout.
+    const int b = ((int)blockIdx.x - 1) * 16 + w;
+    if (b >= n_seq) return;
+    const int32_t* row = am + (size_t)b * seq;
+    int open = 0;
+    for (int i = lane; i < seq; i += 64) open |= row[i];
+    const bool any = __ballot(open != 0) != 0;
+    for (int i = lane; i < seq; i += 64) key_mask[(size_t)b * seq + i] = any ? row[i] : 1;
+    return;
+  }
   // cls_every > 0 (next-sentence head on): the first token of every sequence (t % cls_every == 0)
   // joins the compacted rows even without a label, because the classifier sends a gradient there;
   // its entry in lab stays -100.  counters: [0] rows, [1] error bits, [2] rows with a label.
-  // One workgroup walks the tokens in chunks of 1024 (coalesced); inside a chunk the rank of a
+  // The first workgroup walks the tokens in chunks of 1024 (coalesced); inside a chunk the rank of a
   // predicted position is a wavefront ballot prefix plus the totals of the wavefronts before it.
   __shared__ int wtot[16];
   __shared__ int bad_all;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   if (tid == 0) bad_all = 0;
   __syncthreads();
   int base = 0, bad = 0, labelled = 0;
@@ -168,9 +182,9 @@ __global__ void __launch_bounds__(1024) k_batch_scan(const int32_t* __restrict__
 }
 hipError_t batch_scan(const int32_t* ids, const int32_t* tt, const int32_t* am, const int32_t* labels, int T, int vocab,
                       int type_vocab, int cap, int32_t* pos, int32_t* lab, int32_t* inv, int32_t* counters,
-                      int cls_every, const int32_t* nsp_labels, int n_seq, hipStream_t s) {
-  k_batch_scan<<<dim3(1), dim3(1024), 0, s>>>(ids, tt, am, labels, T, vocab, type_vocab, cap, pos, lab, inv, counters,
-                                              cls_every, nsp_labels, n_seq);
+                      int cls_every, const int32_t* nsp_labels, int n_seq, int32_t* key_mask, hipStream_t s) {
+  k_batch_scan<<<dim3(1 + (n_seq + 15) / 16), dim3(1024), 0, s>>>(ids, tt, am, labels, T, vocab, type_vocab, cap, pos, lab, inv,
+                                                                  counters, cls_every, nsp_labels, n_seq, T / n_seq, key_mask);
   return hipGetLastError();
 }
 
