@@ -16,8 +16,8 @@
 // hold it); the A operand (V^T, K^T, Q^T, dC^T) is written to LDS transposed and in that order.
 // One 256-thread workgroup handles 128 queries (or keys) of one (batch, head): 32 per wavefront.
 // Lengths that are no multiple of 128 run through the same kernels (RAG below).  Before, they went to one wavefront per
-// row in fp32 vector arithmetic: BERT-Base 9+3 layers, 27x203, dropout: attention 12.6 -> 0.7 ms of a step, the step
-// 15.9 -> 4.1 ms.
+// row in fp32 vector arithmetic: BERT-Base 9+3 layers, 27x203, dropout: attention 12.6 -> 0.74 ms of a step, the step
+// 15.9 -> 4.0 ms.
 #include "common.h"
 
 namespace mslt {
@@ -117,6 +117,19 @@ __device__ __forceinline__ f32x16_t zero16() {
 }
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
 
+// The leading eight bits of the values in registers 8c..8c+7 as a B operand, by truncation; they are taken off the
+// registers.  Three in a row hold an fp32 value exactly (24 bits of significand).
+__device__ __forceinline__ bf16x8_t take_frag(f32x16_t& p, int c) {
+  uint32_t u[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t a = __float_as_uint(p[8 * c + 2 * i]), b = __float_as_uint(p[8 * c + 2 * i + 1]);
+    u[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+    p[8 * c + 2 * i] -= __uint_as_float(a & 0xffff0000u);
+    p[8 * c + 2 * i + 1] -= __uint_as_float(b & 0xffff0000u);
+  }
+  return __builtin_bit_cast(bf16x8_t, u32x4_t{u[0], u[1], u[2], u[3]});
+}
 // 4 consecutive d of 32 rows: accumulator block (lane = row index n, registers = d) to global
 // out[(row0 + n)*ld + d0 + 8g + 4half + j] with optional scale, 8-byte stores
 __device__ __forceinline__ void store_acc_T(bf16* __restrict__ out, size_t ld, int n, int half, const f32x16_t& a,
@@ -147,6 +160,30 @@ __device__ __forceinline__ void load_ctx8(const bf16* __restrict__ ctx, const fl
     bf16x8_t v = *reinterpret_cast<const bf16x8_t*>(ctx + o);
 #pragma unroll
     for (int i = 0; i < 8; ++i) c[i] = (float)v[i];
+  }
+}
+
+// acc0, acc1 (d 0..31, 32..63) += rows of the transposed tile times the c-th 16 rows of p (probabilities or their
+// gradients).  Lengths that are a multiple of 128 multiply them in bf16.  The others (RAG) keep the fp32 values, as the
+// wave-per-row kernels that took those lengths before did: three bf16 parts, exact together, for three times the matrix
+// instructions of the second products.  Largest error of the context against float64, as a share of the sum of its
+// terms' magnitudes, 3x203x2 heads: bf16 2^-9.3, in three parts 2^-20.9 (wave-per-row kernels 2^-20).  Per launch at
+// 27x203x12 heads with dropout, bf16 / three parts: forward 36 / 41 us, query side 33 / 37, key side 38 / 46.
+template <bool RAG>
+__device__ __forceinline__ void add_product(f32x16_t& acc0, f32x16_t& acc1, const bf16* tile_t, int n, int blk, int c, int half,
+                                            f32x16_t& p) {
+  const bf16x8_t x0 = frag_transposed(tile_t, n, blk, c, half), x1 = frag_transposed(tile_t, 32 + n, blk, c, half);
+  if constexpr (RAG) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const bf16x8_t f = take_frag(p, c);
+      acc0 = MFMA(x0, f, acc0);
+      acc1 = MFMA(x1, f, acc1);
+    }
+  } else {
+    const bf16x8_t f = pack_frag(p, c);
+    acc0 = MFMA(x0, f, acc0);
+    acc1 = MFMA(x1, f, acc1);
   }
 }
 
@@ -357,11 +394,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_fwd_mfma(const bf16* __restrict
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          bf16x8_t pf = pack_frag(s[j], c);
-          o0 = MFMA(frag_transposed(Vt, n, 2 * kh + j, c, half), pf, o0);
-          o1 = MFMA(frag_transposed(Vt, 32 + n, 2 * kh + j, c, half), pf, o1);
-        }
+        for (int c = 0; c < 2; ++c) add_product<RAG>(o0, o1, Vt, n, 2 * kh + j, c, half, s[j]);
     }
     // (a ragged tile: the swap between the halves below is between lanes of one query, so they leave together)
     if (kt == nkt - 1 && (!RAG || q < S)) {
@@ -461,11 +494,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_q_mfma(const bf16* __restri
         }
       }
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        bf16x8_t df = pack_frag(s, c);
-        dq0 = MFMA(frag_transposed(Kt, n, kb, c, half), df, dq0);
-        dq1 = MFMA(frag_transposed(Kt, 32 + n, kb, c, half), df, dq1);
-      }
+      for (int c = 0; c < 2; ++c) add_product<RAG>(dq0, dq1, Kt, n, kb, c, half, s);
     }
   }
   if (!q_in) return;
@@ -478,7 +507,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_q_mfma(const bf16* __restri
 // (Two wavefronts per SIMD asked for: the accumulators then stay in VGPRs, where the softmax arithmetic reads them
 //  without v_accvgpr moves, and two workgroups share a compute unit.  Unrolled over its four query blocks the plain
 //  kernel takes 53 us at 16x512x12 heads, as a loop 70; the dropout variant spills when unrolled and took 512 registers
-//  with one hash per element: as a loop with shared hashes 41 us at 27x203x12 heads, before 142.)
+//  with one hash per element: as a loop with shared hashes 46 us at 27x203x12 heads, before 142.)
 template <bool DROP, bool RAG>
 __global__ void __launch_bounds__(256, 2) k_attn_bwd_kv_mfma(const bf16* __restrict__ qkv, const bf16* __restrict__ dctx,
                                                           const float* __restrict__ lse,
@@ -552,11 +581,8 @@ __global__ void __launch_bounds__(256, 2) k_attn_bwd_kv_mfma(const bf16* __restr
       }
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        bf16x8_t pf = pack_frag(s, c), df = pack_frag(dp, c);
-        dv0 = MFMA(frag_transposed(Gt, n, qb, c, half), pf, dv0);
-        dv1 = MFMA(frag_transposed(Gt, 32 + n, qb, c, half), pf, dv1);
-        dk0 = MFMA(frag_transposed(Qt, n, qb, c, half), df, dk0);
-        dk1 = MFMA(frag_transposed(Qt, 32 + n, qb, c, half), df, dk1);
+        add_product<RAG>(dv0, dv1, Gt, n, qb, c, half, s);
+        add_product<RAG>(dk0, dk1, Qt, n, qb, c, half, dp);
       }
     }
   }
@@ -673,11 +699,7 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
         }
       }
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        bf16x8_t df = pack_frag(s, c);
-        dq0 = MFMA(frag_transposed(Kt, n, kb, c, half), df, dq0);
-        dq1 = MFMA(frag_transposed(Kt, 32 + n, kb, c, half), df, dq1);
-      }
+      for (int c = 0; c < 2; ++c) add_product<RAG>(dq0, dq1, Kt, n, kb, c, half, s);
     }
     if (RAG && q_own > last) return;
     bf16* out = dqkv + ((size_t)b * S + wave * 32) * ld + h * DH;
@@ -724,11 +746,8 @@ __global__ void __launch_bounds__(512) k_attn_bwd_one_tile(const bf16* __restric
       }
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        bf16x8_t pf = pack_frag(s, c), df = pack_frag(dp, c);
-        dv0 = MFMA(frag_transposed(Gt, n, qb, c, half), pf, dv0);
-        dv1 = MFMA(frag_transposed(Gt, 32 + n, qb, c, half), pf, dv1);
-        dk0 = MFMA(frag_transposed(Qt, n, qb, c, half), df, dk0);
-        dk1 = MFMA(frag_transposed(Qt, 32 + n, qb, c, half), df, dk1);
+        add_product<RAG>(dv0, dv1, Gt, n, qb, c, half, s);
+        add_product<RAG>(dk0, dk1, Qt, n, qb, c, half, dp);
       }
     }
     if (RAG && key_own > last) return;

@@ -87,8 +87,21 @@ def _check(got, ref, mag, lse, precision, label):
         assert (np.abs(got["ctx"] - got["ctx_f32"]) <= 2.0 ** -8 * np.abs(got["ctx_f32"])).all(), label
 
 
+@pytest.mark.parametrize("S", [1, 5, 31, 33, 63, 65, 127, 129, 203, 257, 385])
+@pytest.mark.parametrize("p", [0.0, 0.1])
+def test_bf16_lengths_that_are_no_multiple_of_128_keep_fp32_probabilities(S, p):
+    _check(*_run(3, S, 2, 64, 1, p, seed=100 + S), 1, f"bf16 S={S} p={p}")
+
+
 @pytest.mark.parametrize("S", [1, 31, 33, 128, 161, 257])
 @pytest.mark.parametrize("p", [0.0, 0.1])
 @pytest.mark.parametrize("precision,dh", [(0, 64), (0, 32), (1, 32)])
 def test_fp32_mode_and_other_head_widths(S, p, precision, dh):
     _check(*_run(2, S, 2, dh, precision, p, seed=300 + S), precision, f"precision {precision} dh={dh} S={S} p={p}")
+
+
+# 512 work items (128 queries of one head) have a workgroup each; beyond that a workgroup walks several in sequence
+@pytest.mark.parametrize("B,S,nh", [(300, 33, 2), (70, 129, 4), (140, 130, 4), (26, 203, 12)])
+@pytest.mark.parametrize("p", [0.0, 0.1])
+def test_bf16_forward_workgroups_that_walk_several_work_items(B, S, nh, p):
+    _check(*_run(B, S, nh, 64, 1, p, seed=500 + S), 1, f"bf16 {B}x{S} heads {nh} p={p}")
