@@ -726,9 +726,12 @@ static bool ring_plan(const GemmDesc& d, bool allow_splitk, size_t partial_float
 
 // sum_later: the result is a parameter gradient nothing reads before the optimizer, so a split product may
 // leave its partial sums for the batch at the end of the step
-static int run_gemm(mslt_model* m, const GemmDesc& d, bool allow_splitk = false, hipStream_t st = nullptr,
-                    float* partials = nullptr, bool sum_later = false) {
-  if (!st) { st = m->stream; partials = m->splitk; }
+// at: the stream and that stream's scratch for partial sums, null where there is none (a chain beside the main one)
+struct GemmPlace { hipStream_t st; float* partials; };
+static GemmPlace on_main(const mslt_model* m) { return GemmPlace{m->stream, m->splitk}; }
+static int run_gemm(mslt_model* m, const GemmDesc& d, const GemmPlace& at, bool allow_splitk = false, bool sum_later = false) {
+  const hipStream_t st = at.st;
+  float* const partials = at.partials;
   const bool use_mfma = m->mfma && gemm_mfma_supported(d);
   const double out_esz = d.epi.out_f32 ? 4.0 : (double)m->esz;
   ProfScope ps(m, !use_mfma ? PC_GEMM_SIMT : (d.a_kcontig ? (d.b_kcontig ? PC_GEMM_NT : PC_GEMM_NN) : PC_GEMM_TN),
@@ -793,14 +796,17 @@ static DropSpec dspec(const mslt_model* m, int layer, int site, uint64_t first_e
 // Y[rows,N] = X[rows,K] W[N,K]^T + bias, optional GELU (gelu_grad_out then receives GELU' of the pre-activation),
 // optional dropout of the result
 static int linear_fwd(mslt_model* m, const void* X, int rows, int K, const void* W, int N, const float* bias, void* Y,
-                      int out_f32, int ldo, int act, void* gelu_grad_out, const DropSpec& drop = DropSpec(),
-                      hipStream_t st = nullptr) {
+                      int out_f32, int ldo, int act, void* gelu_grad_out, const DropSpec& drop, const GemmPlace& at) {
   GemmDesc d;
   d.epi.drop = drop; d.epi.drop_ld = N;
   d.A = X; d.lda = K; d.a_kcontig = 1; d.M = rows;
   d.B = W; d.ldb = K; d.b_kcontig = 1; d.N = N; d.K = K;
   d.epi.out = Y; d.epi.ldo = ldo; d.epi.out_f32 = out_f32; d.epi.bias = bias; d.epi.act = act; d.epi.out2 = gelu_grad_out;
-  return run_gemm(m, d, false, st);
+  return run_gemm(m, d, at);
+}
+static int linear_fwd(mslt_model* m, const void* X, int rows, int K, const void* W, int N, const float* bias, void* Y,
+                      int out_f32, int ldo, int act, void* gelu_grad_out) {
+  return linear_fwd(m, X, rows, K, W, N, bias, Y, out_f32, ldo, act, gelu_grad_out, DropSpec(), on_main(m));
 }
 // dX[rows,K] = dY[rows,N] W[N,K]  (+ addend | * gelu'(U))
 // aux_f32 / out_f32: the addend / the result is fp32 whatever the activation type (wide residual gradients)
@@ -811,7 +817,7 @@ static int linear_bwd_input(mslt_model* m, const void* dY, int rows, int N, int 
   d.B = W; d.ldb = K; d.b_kcontig = 0; d.N = K; d.K = N;
   d.epi.out = dX; d.epi.ldo = K; d.epi.act = act; d.epi.aux = aux; d.epi.ldaux = K;
   d.epi.aux_f32 = aux_f32; d.epi.out_f32 = out_f32;
-  return run_gemm(m, d, allow_splitk);
+  return run_gemm(m, d, on_main(m), allow_splitk);
 }
 // dW[N,K] = dY[rows,N]^T X[rows,K]   (fp32 out, contraction over rows)
 // sum_later = false for a tensor that something else writes or adds to later in the same step
@@ -827,7 +833,7 @@ static int linear_bwd_weight(mslt_model* m, const void* dY, int rows, int N, int
   }
   hipStream_t st; float *partials, *red;
   RC(side_fork(m, &st, &partials, &red, again));
-  return run_gemm(m, d, true, st, partials, sum_later);
+  return run_gemm(m, d, GemmPlace{st, partials}, true, sum_later);
 }
 
 static int ln_forward(mslt_model* m, const void* a, const void* r, const float* g, const float* b, void* out, LnStash st,
@@ -864,6 +870,8 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
   const size_t r0 = part ? (size_t)part->b0 * S : 0;          // first token row
   const int rows = part ? nb * S : Tr;
   hipStream_t s = part ? part->st : m->stream;
+  // (two parts run side by side and are planned alike: neither has the scratch of the main stream)
+  const GemmPlace place = part ? GemmPlace{part->st, nullptr} : on_main(m);
   auto at = [&](const void* p, size_t width_bytes) -> void* {   // row r0 of a [rows, width] array (null stays null)
     return p ? (void*)((char*)p + r0 * width_bytes) : nullptr;
   };
@@ -876,7 +884,7 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
   const void* xin = at(Xin, H * e);
   void* xout = at(Xout, H * e);
   RC(linear_fwd(m, xin, rows, H, Wg(m, t_app(m, l, L_WQ)), 3 * H, Wf(m, t_app(m, l, L_BQ)), qkv, 0, 3 * H, EPI_NONE, nullptr,
-                DropSpec(), s));
+                DropSpec(), place));
   AttnDesc a{qkv, ctx, st ? (float*)at(st->lse, (size_t)m->nh * 4) : nullptr, m->key_mask + r0, nb, S, m->nh, m->dh,
              attention_bias(m->cfg.mask_bias), dspec(m, l, SITE_ATTN_PROBS, r0 * m->nh * S), st ? (float*)at(st->ctx32, H * 4) : nullptr};
   {
@@ -885,7 +893,7 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
     HIP_TRY(attention_fwd(m->dtype, a, s));
   }
   RC(linear_fwd(m, ctx, rows, H, Wg(m, t_app(m, l, L_WO)), H, Wf(m, t_app(m, l, L_BO)), y, 0, H, EPI_NONE, nullptr,
-                dspec(m, l, SITE_ATTN_OUT, r0 * H), s));
+                dspec(m, l, SITE_ATTN_OUT, r0 * H), place));
   LnStash s1, s2;
   if (st) {
     s1.xhat = at(st->xhat1, H * e); s1.rstd = (float*)at(st->rstd1, 4);
@@ -893,9 +901,9 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
   }
   RC(ln_forward(m, y, xin, Wf(m, t_app(m, l, L_LN1G)), Wf(m, t_app(m, l, L_LN1B)), x1, s1, rows, s));
   RC(linear_fwd(m, x1, rows, H, Wg(m, t_app(m, l, L_W1)), F, Wf(m, t_app(m, l, L_B1)), g, 0, F, EPI_GELU,
-                st ? at(st->u, F * e) : nullptr, DropSpec(), s));
+                st ? at(st->u, F * e) : nullptr, DropSpec(), place));
   RC(linear_fwd(m, g, rows, F, Wg(m, t_app(m, l, L_W2)), H, Wf(m, t_app(m, l, L_B2)), y, 0, H, EPI_NONE, nullptr,
-                dspec(m, l, SITE_FFN_OUT, r0 * H), s));
+                dspec(m, l, SITE_FFN_OUT, r0 * H), place));
   RC(ln_forward(m, y, x1, Wf(m, t_app(m, l, L_LN2G)), Wf(m, t_app(m, l, L_LN2B)), xout, s2, rows, s));
   return MSLT_OK;
 }
@@ -977,7 +985,7 @@ static int side_flush(mslt_model* m) {
     for (const GemmDesc& d : m->side_dw) {
       RC(side_fork(m, &st, &partials, &red, forked));
       forked = true;
-      RC(run_gemm(m, d, true, st, partials, true));
+      RC(run_gemm(m, d, GemmPlace{st, partials}, true, true));
     }
   }
   for (const auto& c : m->side_cs) {
