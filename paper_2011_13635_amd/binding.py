@@ -132,7 +132,7 @@ def lamb(lr=0.00088, beta1=0.9, beta2=0.999, eps=1e-6, weight_decay=0.01, bias_c
 
 def mslt_debug_gemm(a, b, c, M, N, K, a_kcontig, b_kcontig, kernel, tile_m=0, tile_n=0, tile_k=64, splitk=1,
                     partials=None, stream=None):
-    """One product through a chosen kernel.  a, b: torch bf16 device tensors; c: bf16 or fp32 device tensor
+    """One product through a chosen kernel.  a, b: torch bf16 device tensors (fp32 for kernel 4); c: bf16 or fp32 device tensor
     [M, N]; partials: uint8/fp32 device tensor for split-k.  Enqueues only."""
     import torch
     out_f32 = int(c.dtype == torch.float32)

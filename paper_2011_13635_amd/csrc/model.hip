@@ -1495,16 +1495,20 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
   if (!A || !B || !C) return fail(MSLT_ERR_ARG, "debug_gemm: null operand");
   if (M < 1 || N < 1 || K < 1) return fail(MSLT_ERR_ARG, "debug_gemm: non-positive size");
   if (splitk < 1) return fail(MSLT_ERR_ARG, "debug_gemm: splitk must be at least 1");
-  if (splitk > 1 && (kernel == 0 || !partials || partial_bytes < (size_t)splitk * M * N * 4))
-    return fail(MSLT_ERR_ARG, "debug_gemm: split-k needs kernel 1 or 2 and %zu bytes of partials", (size_t)splitk * M * N * 4);
+  if (splitk > 1 && (!partials || partial_bytes < (size_t)splitk * M * N * 4))
+    return fail(MSLT_ERR_ARG, "debug_gemm: split-k needs %zu bytes of partials", (size_t)splitk * M * N * 4);
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   GemmDesc d;
   d.A = A; d.B = B; d.M = M; d.N = N; d.K = K;
   d.a_kcontig = a_kcontig != 0; d.b_kcontig = b_kcontig != 0;
   d.lda = d.a_kcontig ? K : M; d.ldb = d.b_kcontig ? K : N;
   d.epi.out = C; d.epi.ldo = N; d.epi.out_f32 = out_f32 != 0;
-  if (kernel == 0) {
-    HIP_TRY(gemm_guarded(1, d, 1, nullptr, st));
+  if (kernel == 0 || kernel == 4) {
+    const int dtype = kernel == 0, slab = dtype ? 64 : 32;
+    if (splitk > (K + slab - 1) / slab || (!dtype && !out_f32))
+      return fail(MSLT_ERR_ARG, "debug_gemm: the guarded kernel splits %d into at most %d parts, and fp32 operands give fp32", K,
+                  (K + slab - 1) / slab);
+    HIP_TRY(gemm_guarded(dtype, d, splitk, (float*)partials, st));
   } else if (kernel == 1) {
     if (!gemm_mfma_supported(d) || (tile_m != 0 && tile_m != 128 && tile_m != 256) || (tile_m && M % tile_m) || splitk > K / 64)
       return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d (tile_m %d, splitk %d) not taken by the 128-wide kernel", M, N, K,
@@ -1521,7 +1525,7 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
                   tile_m, tile_n, splitk);
     HIP_TRY(gemm_few(d, tile_m, st));
   } else {
-    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 3");
+    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 4");
   }
   return MSLT_OK;
 }

@@ -73,6 +73,28 @@ def test_guarded_kernel_at_tile_edges(M, N, K, akc, bkc):
     assert np.array_equal(c.cpu().numpy().astype(np.float64), ref)
 
 
+@pytest.mark.parametrize("kernel", [0, 4])
+@pytest.mark.parametrize("M,N,K,splitk", [(70, 65, 300, 1), (70, 65, 300, 2), (70, 65, 300, 3), (70, 65, 300, 5),
+                                          (64, 64, 129, 3), (1, 2, 513, 4), (130, 7, 640, 10), (33, 200, 1024, 7)])
+@pytest.mark.parametrize("akc,bkc", [(1, 1), (1, 0), (0, 0), (0, 1)])
+def test_guarded_kernel_splits_the_contraction_in_both_precisions(kernel, M, N, K, splitk, akc, bkc):
+    # slab counts (64 bf16 or 32 fp32 of k) that the split does not divide, ragged last slabs, an operand of fp32 values
+    # that bf16 does not hold (ten bits); every product and partial sum is exact in fp32, so the results are equal
+    import torch
+    ta, tb, ref = _operands(torch, M, N, K, akc, bkc, seed=60 + M)
+    if kernel == 4:
+        A = ((synth.rand_u64(7, 11, np.arange(M * K)) % 2049).astype(np.float64) - 1024.0).reshape(M, K) / 1024.0
+        B = ((synth.rand_u64(7, 12, np.arange(N * K)) % 3).astype(np.float64) - 1.0).reshape(N, K)
+        ref = A @ B.T
+        ta = torch.tensor(A if akc else A.T.copy(), dtype=torch.float32, device="cuda:0")
+        tb = torch.tensor(B if bkc else B.T.copy(), dtype=torch.float32, device="cuda:0")
+    partials = torch.full((splitk * M * N,), float("nan"), device="cuda:0") if splitk > 1 else None
+    c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda:0")
+    binding.mslt_debug_gemm(ta, tb, c, M, N, K, akc, bkc, kernel, splitk=splitk, partials=partials)
+    torch.cuda.synchronize()
+    assert np.array_equal(c.cpu().numpy().astype(np.float64), ref)
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 128, 64), (128, 768, 128), (384, 256, 576), (256, 384, 3136)])
 @pytest.mark.parametrize("tile", [32, 64])
 @pytest.mark.parametrize("bkc", [1, 0])
@@ -90,7 +112,12 @@ def test_unsupported_choices_are_refused_without_work():
     import torch
     ta, tb, _ = _operands(torch, 256, 256, 128, 1, 1, seed=3)
     c = torch.zeros((256, 256), dtype=torch.float32, device="cuda:0")
-    for args in ((2, 256, 192, 64, 1), (2, 128, 128, 32, 1), (1, 64, 0, 64, 1), (2, 256, 256, 64, 4), (3, 0, 0, 64, 1)):
+    scratch = torch.zeros(3 * 256 * 256, dtype=torch.float32, device="cuda:0")
+    with pytest.raises(binding.MsltError) as ei:      # two slabs of k, three parts
+        binding.mslt_debug_gemm(ta, tb, c, 256, 256, 128, 1, 1, 0, splitk=3, partials=scratch)
+    assert ei.value.code == binding.MSLT_ERR_ARG
+    for args in ((2, 256, 192, 64, 1), (2, 128, 128, 32, 1), (1, 64, 0, 64, 1), (2, 256, 256, 64, 4), (3, 0, 0, 64, 1),
+                 (0, 0, 0, 64, 2), (3, 32, 32, 64, 2), (5, 0, 0, 64, 1)):
         with pytest.raises(binding.MsltError) as ei:
             binding.mslt_debug_gemm(ta, tb, c, 256, 256, 128, 1, 1, args[0], args[1], args[2], args[3], args[4])
         assert ei.value.code == binding.MSLT_ERR_ARG
