@@ -186,6 +186,29 @@ def test_two_stream_schedule_gives_the_single_stream_result_bit_for_bit():
     m.close()
 
 
+@pytest.mark.parametrize("B,S", [(16, 64), (128, 10), (8, 96), (4, 192)])
+def test_two_streams_at_lengths_that_are_no_multiple_of_128(B, S):
+    # the same for the halves of a batch whose attention runs on partly filled tiles; S = 10: rows of the probabilities
+    # start in the middle of a dropout quad, in the second half as in the first
+    from parity_util import make_model
+    sh = synth.bert_base_shape(2)
+    assert B * S * sh.ffn * sh.hidden > 1 << 29 and B * S // 2 % 128 == 0        # the step runs on two chains
+    m = make_model(sh, B, S, 1)
+    m.mslt_load_params(synth.pack_weights(sh, synth.make_weights(sh, seed=8)))
+    cb = m.device_batch(synth.make_batch(sh, B, S, seed=9, ragged=True))
+    for p in (0.0, 0.1):
+        m.mslt_set_dropout(p, 77, 3)
+        l2 = m.mslt_stage_step(1, 1, False, cb)
+        g2, x2 = m.mslt_get_grads().copy(), m.mslt_debug_prefix_output(B, S)
+        m.mslt_profile_enable(True)
+        l1 = m.mslt_stage_step(1, 1, False, cb)
+        g1, x1 = m.mslt_get_grads().copy(), m.mslt_debug_prefix_output(B, S)
+        m.mslt_profile_enable(False)
+        assert l1 == l2, p
+        assert np.array_equal(x1, x2) and np.array_equal(g1, g2), p
+    m.close()
+
+
 def test_a_run_of_training_steps_on_two_streams_gives_the_single_stream_result_bit_for_bit():
     # A run of steps (layer split changing in between, growth, then a step that trains everything) must leave the
     # same parameters whether the kernels are spread over the two streams or all run on one in program order.
