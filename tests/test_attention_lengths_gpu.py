@@ -4,13 +4,12 @@ that are no multiple of four make the dropout quads straddle rows)."""
 import pytest
 
 from paper_2011_13635_amd import synth
-from parity_util import assert_parity, run_case
+from parity_util import TOL, assert_parity, rel_errors, run_case
 
 pytestmark = pytest.mark.gpu
 
-# The bound is the bf16 mode's own (2e-2 of each tensor's largest entry).  Batches hold 400 tokens and more, and at least
-# six sequences, since on fewer (4x203: query-bias gradient 2.9e-2, with scalar fp32 attention 2.88e-2) the handful of
-# roundings behind a small attention gradient scatters past that bound by itself.
+# The bound is the bf16 mode's own (2e-2 of each tensor's largest entry).  Against the oracle on the fp32 masters it is a
+# bound for batches of 400 tokens and six sequences and more, which these are; smaller ones have a test of their own below.
 
 
 @pytest.mark.parametrize("B,S", [(90, 5), (26, 31), (13, 33), (8, 64), (8, 65), (6, 127), (6, 129), (12, 203), (8, 257), (6, 385)])
@@ -28,3 +27,21 @@ def test_fp32_lengths_around_block_edges(B, S, p):
     r = run_case(synth.tiny_shape(3), B, S, 1, 2, False, 0, ragged=True, seed=3, dropout=(p, 7, 2) if p else None)
     assert_parity(r, 0, f"fp32 {B}x{S} dropout {p}")
     r["model"].close()
+
+
+@pytest.mark.parametrize("B,S", [(1, 64), (1, 203), (2, 65), (2, 203), (4, 203)])
+@pytest.mark.parametrize("p", [0.0, 0.1])
+def test_small_batches_against_the_matrices_as_bf16_mode_reads_them(B, S, p):
+    """On one to five sequences few terms stand behind an attention gradient, and two roundings add up in it: that of
+    the weight matrices to bf16 (oracle on rounded against oracle on unrounded matrices: up to 1.3e-2 here) and the
+    kernels' own.  Their sum passes 2e-2 now and then (4x203 with dropout: query-bias gradient 2.7e-2, 2.9e-2 with
+    attention in scalar fp32 arithmetic), which is a limit of the mode at this size.  What the kernels add stays within
+    2e-2 and is what is asserted here."""
+    r = run_case(synth.tiny_shape(3), B, S, 1, 2, False, 1, ragged=True, seed=3, dropout=(p, 7, 2) if p else None,
+                 rounded_oracle=True)
+    r["model"].close()
+    errs = rel_errors(r["grads"], r["rnd_grads"])
+    worst = max(errs, key=errs.get)
+    print(B, S, p, worst, errs[worst], flush=True)
+    assert errs[worst] < TOL[1], (worst, errs[worst])
+    assert abs(r["loss"] - r["rnd_loss"]) < TOL[1] * abs(r["rnd_loss"])
