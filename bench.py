@@ -329,7 +329,7 @@ def main():
                    "trainable_layers": k, "batch": B, "seq_len": S, "tokens_per_step": tokens,
                    "predicted_per_step": int(len(batches[0]["masked_positions"])), "loss": round(float(loss), 5)},
         "roofline": {"bound": "mfma", "kernel": "bf16 MFMA GEMM (k_gemm_ring for forward-type and weight-gradient "
-                     "products, k_gemm_mfma for data-gradient products)", "achieved": round(achieved, 1),
+                     "products, k_gemm_mfma for data-gradient products, k_gemm_few for products of few tiles)", "achieved": round(achieved, 1),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                      "traffic": recorded_gemm_traffic(), "traffic_unit": "bytes per launch (L2-miss side, FETCH_SIZE + "
                      "WRITE_SIZE scaled by a 256 MiB copy)", "algorithmic_bytes_per_launch":

@@ -36,7 +36,9 @@ __device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 7) ^ ((row >
 // A sequence whose length is no multiple of 128 leaves its last tile partly empty (RAG).  Loads of the rows past
 // the end re-read the last row, so that they stay unconditional and in bounds; such keys get a bias of -inf and
 // such queries a log-sum-exp of +inf, either of which makes their probabilities exact zeros, and nothing is stored
-// for them.  Blocks of 32 rows (forward: 64 keys) that lie past the end altogether are skipped.
+// for them.  Blocks of 32 rows (forward: 64 keys) of the side a wavefront walks that lie past the end altogether are
+// skipped.  A wavefront whose own 32 rows do is skipped by the forward and the one-tile backward; in the two-kernel
+// backward it computes on copies of the last row beside the others and stores nothing.
 template <bool RAG>
 __device__ __forceinline__ int tile_row(int row, int last) { return RAG ? min(row, last) : row; }
 

@@ -191,6 +191,13 @@ bool gemm_few_supported(const GemmDesc& d) { return d.a_kcontig && gemm_mfma_sup
 //   128x768x3072 8.4 (32-wide; 64-wide 13.7) / 13.4; 512x768x768 6.7 / 12.0; 1024x768x3072 15.1 / 21.9;
 //   512x3072x768 9.0 / 12.4 and 2048x768x3072 24.8 / 25.1, 384 workgroups; 2048x1024x1024 11.6 / 14.7, 512;
 //   past one round 1024x2304x768 12.7 / 12.6, 1536x2304x768 15.8 / 13.1.
+// At the longest contractions a layer has, this kernel / what the step would take instead: forward (never split over
+// workgroups) 2048x1024x4096, 512 tiles, 33.2 / 40.0, 1024x1024x4096 19.7 / 39.8; the data gradient, which may be split, one
+// workgroup per compute unit 1024x1024x4096 20.5 / 24.4 and 1024x768x3072 16.8 / 20.7, but with two, from K = 3072 on, about
+// even: 1536x768x3072 22.3 / 21.0, 2688x768x3072 27.7 / 26.5, 1280x1024x4096 28.0 / 24.9, 2048x1024x4096 33.9 / 36.8,
+// 2048x1024x3072 25.5 / 31.4.  The 32-wide form meets a split by 8 near K = 8192 (data gradient 128x768: 8192 18.7 / 18.9,
+// 12288 26.4 / 22.7) and the 64-wide one between 6144 and 8192 (forward 1024x1024x6144 25.6 / 28.9, 1024x768x8192 30.8 / 26.9);
+// past 4096 only products over the vocabulary are that long.
 // Two 64-wide workgroups on a compute unit with one group in flight beat one with two in flight: 512x3072x768 9.0
 // against 13.7.  A long contraction is better split over workgroups: at 512x768x30592 the 64-wide form took 154, a
 // split by 8 of the 128-wide kernel 53.

@@ -40,9 +40,9 @@ enum { H_WT = 0, H_BT, H_LNG, H_LNB, H_BOUT, N_HEAD };
 enum { P_W = N_HEAD, P_B, C_W, C_B, N_HEAD_NSP };
 
 // Optional per-kernel-class timing with HIP events on the model's stream (off by default).
-enum ProfClass { PC_GEMM_NT = 0, PC_GEMM_NN, PC_GEMM_TN, PC_GEMM_SIMT, PC_ATTN_FWD, PC_ATTN_BWD, PC_LN_FWD, PC_LN_BWD,
+enum ProfClass { PC_GEMM_NT = 0, PC_GEMM_NN, PC_GEMM_TN, PC_GEMM_GUARDED, PC_ATTN_FWD, PC_ATTN_BWD, PC_LN_FWD, PC_LN_BWD,
                  PC_COLSUM, PC_EMBED, PC_HEAD_MISC, PC_CE, PC_EMBED_BWD, PC_OPT, PC_REDUCE, PC_COUNT };
-static const char* kProfNames[PC_COUNT] = {"gemm_mfma_nt", "gemm_mfma_nn", "gemm_mfma_tn", "gemm_simt", "attention_fwd",
+static const char* kProfNames[PC_COUNT] = {"gemm_mfma_nt", "gemm_mfma_nn", "gemm_mfma_tn", "gemm_guarded", "attention_fwd",
                                            "attention_bwd", "layernorm_fwd", "layernorm_bwd", "bias_colsum", "embed_fwd",
                                            "head_gather_scatter", "cross_entropy", "embed_bwd", "optimizer", "gradient_sums"};
 static int pick_splitk(int M, int N, int K);
@@ -734,7 +734,7 @@ static int run_gemm(mslt_model* m, const GemmDesc& d, const GemmPlace& at, bool 
   float* const partials = at.partials;
   const bool use_mfma = m->mfma && gemm_mfma_supported(d);
   const double out_esz = d.epi.out_f32 ? 4.0 : (double)m->esz;
-  ProfScope ps(m, !use_mfma ? PC_GEMM_SIMT : (d.a_kcontig ? (d.b_kcontig ? PC_GEMM_NT : PC_GEMM_NN) : PC_GEMM_TN),
+  ProfScope ps(m, !use_mfma ? PC_GEMM_GUARDED : (d.a_kcontig ? (d.b_kcontig ? PC_GEMM_NT : PC_GEMM_NN) : PC_GEMM_TN),
                2.0 * d.M * d.N * d.K, ((double)d.M * d.K + (double)d.N * d.K) * m->esz + (double)d.M * d.N * out_esz);
   // Which kernel takes which product was settled by measuring whole steps (two kernel chains run side by
   // side there, so a kernel's footprint counts as much as its own speed): forward-type products (both
@@ -1160,14 +1160,19 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   }
   // The two halves of the batch go through the encoder as two independent chains of kernels, one per
   // stream: where a kernel of one chain leaves compute units idle (a last, partly filled round of
-  // workgroups, its ramp-up and its drain) kernels of the other chain take them.  Measured: 2-5 %
-  // of the step; four chains on four streams were slower.  Dropout indexes its decisions by position
+  // workgroups, its ramp-up and its drain) kernels of the other chain take them; four chains on four
+  // streams were slower.  Dropout indexes its decisions by position
   // in the whole batch: the second half's kernels get keys that carry its offset (S even keeps the
   // offset of the attention probabilities a multiple of 4).  Off while event profiling.
   // (queued as one chain then, with the kernels the halves would take, so that the results are the same bits)
-  // One chain where the widest product has at most 2^30 operations: such a product lasts about as long as its launch,
-  // and a second chain only doubles the launches the host has to queue.  Two chains / one, us: 128-wide 2+1 layer model
-  // 4x64 408 / 313, 32x64 446 / 342, 64x128 (2^30) 461 / 445; BERT-Base 2x128 (1.1 * 2^30) 1192 / 1234.
+  // One chain where the widest product, a feed-forward one, has at most 2^30 operations: such a product lasts about as
+  // long as its launch, and a second chain only doubles the launches the host has to queue.  Two chains / one, us:
+  //   at the line and below (at most 2^30): 128-wide 2+1 layers 4x64 358 / 289, 32x64 368 / 331, 64x128 421 / 424; 256-wide
+  //   4+2 2x128 573 / 519, 16x128 650 / 629; 512-wide 4+2 4x128 650 / 625;
+  //   above it: Base 9+3 2x128 (1.1 * 2^30) 1152 / 1170, 4x128 1274 / 1325, 8x128 1504 / 1611, 16x128 1866 / 1886, 64x128
+  //   3723 / 4228; Large 18+6 2x128 2554 / 2607, 8x128 3584 / 3763, 32x128 7359 / 7378; 256-wide 32x128 774 / 791.
+  // 512-wide models from 1.5 to 8 times the line are the exception (one chain ahead by up to 4 %, 8x128 771 / 742): no
+  // line by operations parts them from Base at 2x128.
   const bool two_chains = m->dtype == 1 && m->mfma && B % 2 == 0 && (T / 2) % 128 == 0 && Tr == T && S % 2 == 0 &&
                           (double)T * m->F * H > (double)(1 << 29);
   const bool halves = two_chains && !m->prof.on;

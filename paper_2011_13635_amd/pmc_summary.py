@@ -1,5 +1,5 @@
 """Summarises two rocprofv3 --pmc runs of bench.py (FETCH_SIZE, WRITE_SIZE; csv output) into the HBM-side traffic of
-the MFMA GEMM kernel per launch, scaled by what the same counters read for the plain 256 MiB device copy that
+the MFMA GEMM kernels per launch, scaled by what the same counters read for the plain 256 MiB device copy that
 `bench.py --copy-calibration` issues.  Also records the hash of the kernel source so that bench.py can tell
 whether the figure still belongs to the kernel it times.
 
@@ -21,9 +21,10 @@ import re
 import sys
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
-KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("gemm_ring.hip", "gemm_mfma.hip", "gemm_epilogue.h", "common.h")]
+KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("gemm_ring.hip", "gemm_mfma.hip", "gemm_few.hip", "gemm_epilogue.h",
+                                                  "common.h")]
 ROWWISE_SOURCES = [os.path.join(CSRC, f) for f in ("rowwise.hip", "attention_mfma.hip", "common.h")]
-GEMM_KERNELS = ("k_gemm_mfma", "k_gemm_ring")
+GEMM_KERNELS = ("k_gemm_mfma", "k_gemm_ring", "k_gemm_few")
 COPY_BYTES = 256 * 1024 * 1024
 
 

@@ -24,7 +24,7 @@ def test_tiny_with_dropout(precision, f, k, emb):
 
 @pytest.mark.parametrize("precision", [0, 1])
 def test_unaligned_with_dropout(precision):
-    # guarded kernels (wave-per-row attention, SIMT products), a high rate
+    # guarded kernels (wave-per-row attention, guarded products), a high rate
     sh = small_shape(2)
     std, perturb = (0.2, 0.2) if precision == 0 else (0.05, 0.05)
     r = run_case(sh, 11, 13, 0, 2, True, precision, ragged=True, seed=5, std=std, perturb=perturb, dropout=(0.25, 3, 0))
