@@ -1,6 +1,6 @@
 // Guarded reference attention kernels (any sequence length, head width up to 128): one
 // wavefront per query row (forward, dQ) or per key row (dK, dV).  Used in both modes for head widths
-// other than 64, which the matrix-core kernels do not take.  Scores are recomputed in
+// other than 64, which the matrix-core kernels do not take, and for very short sequences.  Scores are recomputed in
 // the backward from Q, K and the stored row log-sum-exp; no S x S matrix ever reaches memory.
 #include "common.h"
 

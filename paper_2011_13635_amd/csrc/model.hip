@@ -844,14 +844,31 @@ static int ln_forward(mslt_model* m, const void* a, const void* r, const float* 
 }
 
 // ---- attention dispatch ---------------------------------------------------------------------
+// The matrix-core kernels own whole blocks of rows (bf16 128, fp32 32 of one head), so on very short sequences most of
+// their work is padding, and one wavefront per row is faster up to a length that depends on the arithmetic beside it.
+// Matrix-core / wave-per-row, us, 8192 tokens x 12 heads, at the lengths below and at the line:
+//   bf16 forward 1170x7 88 / 83, 1024x8 76 / 79; with dropout 910x9 95 / 86, 819x10 87 / 89;
+//   bf16 backward 910x9 209 / 195, 819x10 191 / 205; with dropout 819x10 231 / 205, 744x11 208 / 212;
+//   fp32 forward 910x9 101 / 91, 819x10 94 / 96; with dropout 744x11 106 / 103, 682x12 89 / 105;
+//   fp32 backward 630x13 390 / 355, 585x14 365 / 375; with dropout 585x14 424 / 376, 512x16 358 / 426.
+// At one token the ratio is 8 to 28 (bf16 backward 8192x1 1800 / 145, fp32 4478 / 188).  The lines are about the same at
+// 2048 tokens; at 256 all of them take one launch's latency.
+static int attention_line(int dtype, bool backward, bool drop) {
+  static const int line[2][2][2] = {{{10, 12}, {14, 16}}, {{8, 10}, {10, 11}}};   // [fp32, bf16][forward, backward][dropout]
+  return line[dtype][backward][drop];
+}
 static hipError_t attention_fwd(int dtype, const AttnDesc& a, hipStream_t s) {
-  if (dtype == 1 && attention_mfma_supported(a.S, a.dh)) return attention_fwd_mfma(a, s);
-  if (dtype == 0 && attention_f32_supported(a.dh)) return attention_fwd_f32(a, s);
+  if (a.S >= attention_line(dtype, false, a.drop.thr != 0)) {
+    if (dtype == 1 && attention_mfma_supported(a.S, a.dh)) return attention_fwd_mfma(a, s);
+    if (dtype == 0 && attention_f32_supported(a.dh)) return attention_fwd_f32(a, s);
+  }
   return attention_fwd_simple(dtype, a, s);
 }
 static hipError_t attention_bwd(int dtype, const AttnBwdDesc& a, hipStream_t s) {
-  if (dtype == 1 && attention_mfma_supported(a.S, a.dh)) return attention_bwd_mfma(a, s);
-  if (dtype == 0 && attention_f32_supported(a.dh)) return attention_bwd_f32(a, s);
+  if (a.S >= attention_line(dtype, true, a.drop.thr != 0)) {
+    if (dtype == 1 && attention_mfma_supported(a.S, a.dh)) return attention_bwd_mfma(a, s);
+    if (dtype == 0 && attention_f32_supported(a.dh)) return attention_bwd_f32(a, s);
+  }
   return attention_bwd_simple(dtype, a, s);
 }
 
