@@ -243,9 +243,10 @@ int mslt_profile_read(mslt_model* m, mslt_profile_entry* out, int cap, int* n);
  * shape), 128 or 256; M % 128 == 0, N % 128 == 0, K % 64 == 0.  kernel 2: large-tile kernel fed by
  * direct global-to-LDS loads, tile_m x tile_n one of 256x256, 256x128, 128x256, 128x128, ring stage
  * tile_k 64 (or 32, not for 128x128); M % tile_m == 0, N % tile_n == 0, K % tile_k == 0.  kernel 3:
- * few-tile kernel, a_kcontig != 0, sizes as kernel 1, tile_m = tile_n = 32 or 64.  splitk > 1
- * (not kernel 3) splits the contraction over workgroups and needs `partials`, DEVICE scratch of at
- * least splitk*M*N*4 bytes (partial_bytes says how large it is).  Returns MSLT_ERR_ARG for a shape or
+ * few-tile kernel, a_kcontig != 0, sizes as kernel 1, tile_m = tile_n = 32 or 64.  kernel 5: the tiles a step uses where
+ * the rows of C are no multiple of the tile, a_kcontig != 0, any M, N % tile_n == 0 (128 at least), K % 64 == 0: 256x256,
+ * 256x384, 256x128, 128x256, 128x192, 64x64 or 32x32.  splitk > 1 (not kernels 3 and 5) splits the contraction over
+ * workgroups and needs `partials`, DEVICE scratch of at least splitk*M*N*4 bytes (partial_bytes says how large it is).  Returns MSLT_ERR_ARG for a shape or
  * choice the kernel does not take; nothing is enqueued then.  Does not block. */
 int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, void* C, int M, int N, int K, int a_kcontig,
                     int b_kcontig, int out_f32, int kernel, int tile_m, int tile_n, int tile_k, int splitk,

@@ -99,6 +99,11 @@ __device__ inline void gelu_parts_fast(float u, float& cdf, float& pdf) {
   cdf = u >= 0.f ? 1.0f - erfc_half : erfc_half;
   pdf = 0.39894228040143267794f * e;
 }
+__device__ inline float gelu_fast(float u) {
+  float c, p;
+  gelu_parts_fast(u, c, p);
+  return u * c;
+}
 // value and derivative together (the forward epilogue stores the derivative for the backward pass)
 __device__ inline void gelu_both_fast(float u, float& val, float& grad) {
   float c, p;
@@ -153,16 +158,18 @@ hipError_t gemm_guarded(int dtype, const GemmDesc& d, int splitk, float* partial
 // bounds by construction (padded buffers).  splitk > 1 writes fp32 partials to `partials`
 // ([splitk][M][N]) and reduces them in fixed order into the epilogue.
 bool gemm_mfma_supported(const GemmDesc& d);
+bool gemm_rows_supported(const GemmDesc& d);   // the same for any M, for kernels that guard the rows of C
 // force_tile_m: 0 = choose the M-tile height (128 or 256 rows) from the shape.
 int gemm_mfma_tile_m(const GemmDesc& d);
 // force_dma: -1 = default choice, 0/1 = k-contiguous operands through registers / direct to LDS.
 hipError_t gemm_mfma(const GemmDesc& d, int splitk, float* partials, hipStream_t s, int force_tile_m = 0,
                      int force_dma = -1);
 
-// Large-tile MFMA kernel (bf16 only): tile_m x tile_n of 256x256, 256x128 or 128x256, both operands loaded
-// global -> LDS directly in any of the three layouts; M % tile_m == 0, N % tile_n == 0.
+// Large-tile MFMA kernel (bf16 only): tile_m x tile_n of 256x256, 256x128, 128x256 or 128x128, both operands loaded
+// global -> LDS directly in any of the three layouts; M % tile_m == 0 (with any_rows and a k-contiguous A any M: rows past
+// the end are neither read nor written), N % tile_n == 0.
 // rk: k extent of a ring stage, 32 or 64 (K % rk == 0).
-bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk);
+bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk, bool any_rows = false);
 // Up to gemm_ring_group_max() products whose operands are both k-strided (weight gradients) as one launch of
 // tile_m x tile_n tiles (128x128, 256x128 or 256x256), none of them split; each must pass
 // gemm_ring_supported(d, tile_m, tile_n, 64).
@@ -173,7 +180,16 @@ hipError_t gemm_ring_grouped_tn(const GemmDesc* d, int n, int tile_m, int tile_n
 hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int splitk, float* partials, hipStream_t s,
                      bool keep_partials = false);
 
-// Kernel for products with few output tiles (bf16, A k-contiguous; sizes as gemm_mfma_supported): tile x tile output
+// Large tiles whose wavefronts take turns (bf16): 256x256 in any operand layout; 256x384, 256x128 and 128x192 with a
+// k-contiguous A.  Any M when A is k-contiguous (rows past the end are neither read nor written), N % tile_n == 0,
+// K % 64 == 0.  Only 256x256 and 256x128 split the contraction; keep_partials as in gemm_ring.
+bool gemm_phase_supported(const GemmDesc& d, int tile_m, int tile_n);
+hipError_t gemm_phase(const GemmDesc& d, int tile_m, int tile_n, int splitk, float* partials, hipStream_t s,
+                      bool keep_partials = false);
+// as gemm_ring_grouped_tn, with tiles of 256x256
+hipError_t gemm_phase_grouped_tn(const GemmDesc* d, int n, hipStream_t s);
+
+// Kernel for products with few output tiles (bf16, A k-contiguous; sizes as gemm_rows_supported): tile x tile output
 // tiles, 32 or 64, the contraction split among the wavefronts of a workgroup.
 bool gemm_few_supported(const GemmDesc& d);
 // Tile it should take a product with, 0: another kernel should.  rows: d.M, or the rows of the part of a product that

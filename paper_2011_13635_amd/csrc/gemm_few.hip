@@ -35,7 +35,9 @@ struct Params {
   Epilogue epi;
 };
 
-template <int TM, int TN, int W, int D, bool B_KC>
+// RAGGED: M is no multiple of TM.  (The clamped row addresses cost 1.5 to 2 us of 13 at 512x1024x1024, so whole tiles keep
+// theirs: one offset a lane, everything else uniform.)
+template <int TM, int TN, int W, int D, bool B_KC, bool RAGGED>
 __global__ void __launch_bounds__(64 * W, 2) k_gemm_few(Params p) {
   constexpr int RM = TM / 16, RN = TN / 16;
   constexpr int LDR = TN + 4;                       // floats per row of a partial tile
@@ -65,7 +67,10 @@ __global__ void __launch_bounds__(64 * W, 2) k_gemm_few(Params p) {
     constexpr int LB = TN / 8;
     const int lr = lane >> 3, lc = lane & 7;
     // (the lane's part of an address is one 32-bit offset, everything else of it uniform)
-    const unsigned oa = (unsigned)(lr * p.lda + 8 * lc);
+    // (rows past the end of A, of a last tile that is not full, repeat the last one; their results are not written)
+    unsigned oa[RAGGED ? NA : 1];
+#pragma unroll
+    for (int a = 0; a < (RAGGED ? NA : 1); ++a) oa[a] = (unsigned)((RAGGED ? min(8 * a + lr, p.M - 1 - m0) : lr) * p.lda + 8 * lc);
     const unsigned ob = B_KC ? (unsigned)(lr * p.ldb + 8 * lc) : (unsigned)((lane / LB) * p.ldb + (lane % LB) * 8);
     const bf16* ua = p.A + (size_t)m0 * p.lda;
     const bf16* ub = B_KC ? p.B + (size_t)n0 * p.ldb : p.B + n0;
@@ -73,7 +78,7 @@ __global__ void __launch_bounds__(64 * W, 2) k_gemm_few(Params p) {
     auto load = [&](int slot, int i) {               // i-th group of this wavefront
       const int k = 64 * (wave + W * i);
 #pragma unroll
-      for (int a = 0; a < NA; ++a) fa[slot][a] = *reinterpret_cast<const u32x4_t*>(ua + (size_t)(8 * a) * p.lda + k + oa);
+      for (int a = 0; a < NA; ++a) fa[slot][a] = *reinterpret_cast<const u32x4_t*>(RAGGED ? ua + k + oa[RAGGED ? a : 0] : ua + (size_t)(8 * a) * p.lda + k + oa[0]);
 #pragma unroll
       for (int b = 0; b < NB; ++b)
         fb[slot][b] = *reinterpret_cast<const u32x4_t*>((B_KC ? ub + (size_t)(8 * b) * p.ldb + k : ub + (size_t)(k + b * (64 / LB)) * p.ldb) + ob);
@@ -147,7 +152,7 @@ __global__ void __launch_bounds__(64 * W, 2) k_gemm_few(Params p) {
 #pragma unroll
     for (int u = 0; u < TURNS; ++u) {
       const int x = (int)threadIdx.x + u * 64 * W;
-      if (x < SPANS) raw[u] = load_aux8(e, m0 + x / (TN / 8), n0 + (x % (TN / 8)) * 8);
+      if (x < SPANS && (!RAGGED || m0 + x / (TN / 8) < p.M)) raw[u] = load_aux8(e, m0 + x / (TN / 8), n0 + (x % (TN / 8)) * 8);
     }
   }
   __syncthreads();
@@ -156,6 +161,7 @@ __global__ void __launch_bounds__(64 * W, 2) k_gemm_few(Params p) {
     const int x = (int)threadIdx.x + u * 64 * W;
     if (x >= SPANS) break;
     const int row = x / (TN / 8), col = (x % (TN / 8)) * 8;
+    if (RAGGED && m0 + row >= p.M) continue;
     float v[8] = {0, 0, 0, 0, 0, 0, 0, 0}, bias[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
@@ -176,13 +182,18 @@ __global__ void __launch_bounds__(64 * W, 2) k_gemm_few(Params p) {
 template <int TM, int TN, int W, int D>
 static void launch(const GemmDesc& d, const Params& p, hipStream_t s) {
   const dim3 grid((unsigned)(((p.tiles_m * p.tiles_n + 7) / 8) * 8)), block(64 * W);
-  if (d.b_kcontig) k_gemm_few<TM, TN, W, D, true><<<grid, block, 0, s>>>(p);
-  else k_gemm_few<TM, TN, W, D, false><<<grid, block, 0, s>>>(p);
+  if (d.M % TM) {
+    if (d.b_kcontig) k_gemm_few<TM, TN, W, D, true, true><<<grid, block, 0, s>>>(p);
+    else k_gemm_few<TM, TN, W, D, false, true><<<grid, block, 0, s>>>(p);
+  } else {
+    if (d.b_kcontig) k_gemm_few<TM, TN, W, D, true, false><<<grid, block, 0, s>>>(p);
+    else k_gemm_few<TM, TN, W, D, false, false><<<grid, block, 0, s>>>(p);
+  }
 }
 
 }  // namespace few
 
-bool gemm_few_supported(const GemmDesc& d) { return d.a_kcontig && gemm_mfma_supported(d); }
+bool gemm_few_supported(const GemmDesc& d) { return d.a_kcontig && gemm_rows_supported(d); }
 
 // Tile edge for a product, 0 when another kernel should take it.  The chip holds 256 workgroups of the 32-wide form and
 // 512 of the 64-wide one at a time; past one such round the wide kernels' fewer bytes per FLOP win, and within it the
@@ -212,7 +223,7 @@ int gemm_few_tile(const GemmDesc& d, int rows) {
 hipError_t gemm_few(const GemmDesc& d, int tile, hipStream_t s) {
   if (!gemm_few_supported(d) || (tile != 32 && tile != 64)) return hipErrorInvalidValue;
   few::Params p{reinterpret_cast<const bf16*>(d.A), reinterpret_cast<const bf16*>(d.B), d.M, d.N, d.K, d.lda, d.ldb,
-                d.M / tile, d.N / tile, d.epi};
+                (d.M + tile - 1) / tile, d.N / tile, d.epi};
   if (tile == 32) few::launch<32, 32, 8, 3>(d, p, s);
   else few::launch<64, 64, 4, 1>(d, p, s);
   return hipGetLastError();

@@ -202,13 +202,16 @@ __global__ void __launch_bounds__(2 * BM) k_gemm_mfma(MfmaParams p) {
   const int kbeg = kt_lo * BK;
   const int nk = (int)((long long)(split + 1) * nkt / p.splitk) - kt_lo;
 
+  // the accumulators start from the bias of the lane's column, as in the large tiles (the same bits whichever is taken)
   f32x16_t acc[2][2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 2; ++j) {
+    const float b0 = p.epi.bias && p.splitk == 1 ? p.epi.bias[n0 + 64 * wn + 32 * j + (lane & 31)] : 0.f;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = b0;
+  }
 
   // Software pipeline: PF register sets hold the slabs of tiles kt+1 .. kt+PF while tile kt is
   // multiplied out of LDS.  Tile t lives in set t % PF; the loop is unrolled by PF so that every
@@ -287,15 +290,13 @@ __global__ void __launch_bounds__(2 * BM) k_gemm_mfma(MfmaParams p) {
   for (int j = 0; j < PF - 1; ++j)
     if (kt + j < nk) body(ra[j], rb[j], ra[(j + 1) % PF], rb[(j + 1) % PF], kt + j);
 
-  // Epilogue operands first: the bias and the per-element operand are requested before the
-  // accumulators are staged, so their memory latency runs under the staging and its barrier.
+  // Epilogue operands first: the per-element operand is requested before the accumulators are staged, so its memory
+  // latency runs under the staging and its barrier.
   const int cc = 8 * (lane & 7);
   const int n = n0 + 64 * wn + cc;
   const int mrow = m0 + 64 * wm + (lane >> 3);      // first of this lane's 8 rows (stride 8)
   Epilogue e = p.epi;
-  float bias[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) bias[i] = 0.f;
+  const float bias[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // already in the accumulators
   uint4 raw[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) raw[i] = make_uint4(0, 0, 0, 0);
@@ -308,11 +309,6 @@ __global__ void __launch_bounds__(2 * BM) k_gemm_mfma(MfmaParams p) {
     if (epilogue_reads_aux(e)) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) raw[i] = load_aux8(e, mrow + 8 * i, n);
-    }
-    if (e.bias) {
-      float4 b0 = *reinterpret_cast<const float4*>(e.bias + n), b1 = *reinterpret_cast<const float4*>(e.bias + n + 4);
-      bias[0] = b0.x; bias[1] = b0.y; bias[2] = b0.z; bias[3] = b0.w;
-      bias[4] = b1.x; bias[5] = b1.y; bias[6] = b1.z; bias[7] = b1.w;
     }
   }
 
@@ -367,9 +363,10 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(const float* __restrict__
   else epilogue8<false>(e, m, n, v, bias, raw);
 }
 
-bool gemm_mfma_supported(const GemmDesc& d) {
+bool gemm_mfma_supported(const GemmDesc& d) { return d.M % 128 == 0 && gemm_rows_supported(d); }
+bool gemm_rows_supported(const GemmDesc& d) {
   if (d.M <= 0 || d.N <= 0 || d.K <= 0) return false;
-  if (d.M % 128 || d.N % BN || d.K % BK) return false;
+  if (d.N % BN || d.K % BK) return false;
   if (d.lda % 8 || d.ldb % 8 || d.epi.ldo % 8) return false;
   if ((d.epi.act == EPI_MUL || d.epi.act == EPI_ADD) && d.epi.ldaux % 8) return false;
   if (d.epi.drop.thr && d.epi.drop_ld % 4) return false;

@@ -1,5 +1,7 @@
 // Large-tile bf16 MFMA GEMM for gfx950: C(m,n) = sum_k A(m,k) B(n,k), fp32 accumulation, shared
-// epilogue.  Made for the products of the training step that have enough output tiles: the
+// epilogue.  A step takes the tiles of gemm_phase.hip where they are the faster ones, and from here 128x256 for narrow
+// outputs (8192x1024x1024 17 us, 128x192 of that file does not divide 1024, its 256x128 22) and 128x128 and 256x128 for the
+// weight gradients of smaller models.  Made for the products of the training step that have enough output tiles: the
 // operand feed (global memory -> vector L1 -> LDS) is what bounds a 128x128 tile, and a 256x256
 // tile moves half the bytes per MFMA.
 //
@@ -209,20 +211,27 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
   // column m0 of [k][ld]); every offset below stays far under 2^31 (checked on the host)
   const bf16* abase = A_KC ? p.A + (size_t)m0 * p.lda : p.A + m0;
   const bf16* bbase = B_KC ? p.B + (size_t)n0 * p.ldb : p.B + n0;
-  __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)abase, 0, 0x7fffffff, 0x00020000);
+  // (the view of a k-contiguous A ends with its last row: rows past it, of a last tile that is not full, read as zeros)
+  const long long a_left = ((long long)(p.M - m0 - 1) * p.lda + p.K) * 2;
+  const int a_bytes = A_KC && a_left < 0x7fffffff ? (int)a_left : 0x7fffffff;
+  __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)abase, 0, a_bytes, 0x00020000);
   __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)bbase, 0, 0x7fffffff, 0x00020000);
   MoverA ma; ma.init(lane, p.lda);
   MoverB mb; mb.init(lane, p.ldb);
   FragsA fa; fa.init(lane, WTM * wm);
   FragsB fb; fb.init(lane, WTN * wn);
 
+  // the accumulators start from the bias of the lane's column, as those of gemm_phase.hip do: a product is the same bits
+  // whichever of these tiles it goes to
   f32x16_t acc[MI][NI];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int j = 0; j < NI; ++j) {
+    const float b0 = p.epi.bias && p.splitk == 1 ? p.epi.bias[n0 + WTN * wn + 32 * j + (lane & 31)] : 0.f;
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = b0;
+  }
 
   // tile t lives in stage t % NS; indices past the end are clamped (their loads land in a stage nobody
   // reads any more), which keeps the count of loads in flight the same in every iteration
@@ -312,14 +321,7 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
     e.out_f32 = 1;
   }
   const int n = n0 + WTN * wn + cc;
-  float bias[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) bias[i] = 0.f;
-  if (e.bias) {
-    float4 q0 = *reinterpret_cast<const float4*>(e.bias + n), q1 = *reinterpret_cast<const float4*>(e.bias + n + 4);
-    bias[0] = q0.x; bias[1] = q0.y; bias[2] = q0.z; bias[3] = q0.w;
-    bias[4] = q1.x; bias[5] = q1.y; bias[6] = q1.z; bias[7] = q1.w;
-  }
+  const float bias[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // already in the accumulators
   float* stage = reinterpret_cast<float*>(smem) + wave * 64 * EPI_LD;
 #pragma unroll
   for (int pass = 0; pass < MI / 2; ++pass) {
@@ -329,7 +331,8 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
     for (int i = 0; i < 8; ++i) raw[i] = make_uint4(0, 0, 0, 0);
     if (epilogue_reads_aux(e)) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) raw[i] = load_aux8(e, mrow + 8 * i, n);
+      for (int i = 0; i < 8; ++i)
+        if (mrow + 8 * i < p.M) raw[i] = load_aux8(e, mrow + 8 * i, n);
     }
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
@@ -345,6 +348,7 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         int row = 8 * i + (lane >> 3);
+        if (mrow + 8 * i >= p.M) continue;
         float4 x0 = *reinterpret_cast<const float4*>(stage + row * EPI_LD + cc);
         float4 x1 = *reinterpret_cast<const float4*>(stage + row * EPI_LD + cc + 4);
         float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
@@ -389,9 +393,7 @@ constexpr int ring_depth(int TM, int TN, int RK) {
   template __global__ void k_gemm_ring<TM, TN, RK, ring_depth(TM, TN, RK), false, true>(Params);  \
   template __global__ void k_gemm_ring<TM, TN, RK, ring_depth(TM, TN, RK), false, false>(Params);
 template __global__ void k_gemm_ring_grouped<128, 128, 64, ring_depth(128, 128, 64), false, false>(GroupParams);
-template __global__ void k_gemm_ring_grouped<256, 256, 64, ring_depth(256, 256, 64), false, false>(GroupParams);
 template __global__ void k_gemm_ring_grouped<256, 128, 64, ring_depth(256, 128, 64), false, false>(GroupParams);
-MSLT_RING_INSTANCES(256, 256, 64)
 MSLT_RING_INSTANCES(256, 128, 64)
 MSLT_RING_INSTANCES(128, 256, 64)
 MSLT_RING_INSTANCES(128, 128, 64)
@@ -466,11 +468,11 @@ hipError_t gemm_ring_grouped_tn(const GemmDesc* d, int n, int tile_m, int tile_n
   if (n < 1 || n > ring::GROUP_MAX) return hipErrorInvalidValue;
   if (tile_m == 128 && tile_n == 128) return grouped_tn<128, 128>(d, n, s);
   if (tile_m == 256 && tile_n == 128) return grouped_tn<256, 128>(d, n, s);
-  if (tile_m == 256 && tile_n == 256) return grouped_tn<256, 256>(d, n, s);
+  if (tile_m == 256 && tile_n == 256) return gemm_phase_grouped_tn(d, n, s);
   return hipErrorInvalidValue;
 }
 
-bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk) {
+bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk, bool any_rows) {
   if (rk != 32 && rk != 64) return false;
   if (d.M <= 0 || d.N <= 0 || d.K <= 0) return false;
   if (d.lda % 8 || d.ldb % 8 || d.epi.ldo % 8) return false;
@@ -482,7 +484,7 @@ bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk) {
   if (!((tile_m == 256 && tile_n == 256) || (tile_m == 256 && tile_n == 128) || (tile_m == 128 && tile_n == 256) ||
         (tile_m == 128 && tile_n == 128 && rk == 64)))
     return false;
-  if (d.M % tile_m || d.N % tile_n || d.K % rk) return false;
+  if ((d.M % tile_m && !(any_rows && d.a_kcontig)) || d.N % tile_n || d.K % rk) return false;
   // byte offsets inside a tile's buffer view stay below 2^31
   const long long a_span = d.a_kcontig ? (long long)tile_m * d.lda + d.K : (long long)d.K * d.lda + tile_m;
   const long long b_span = d.b_kcontig ? (long long)tile_n * d.ldb + d.K : (long long)d.K * d.ldb + tile_n;
@@ -492,7 +494,8 @@ bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk) {
 
 hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int splitk, float* partials, hipStream_t s,
                      bool keep_partials) {
-  if (!gemm_ring_supported(d, tile_m, tile_n, rk)) return hipErrorInvalidValue;
+  if (!gemm_ring_supported(d, tile_m, tile_n, rk, splitk == 1)) return hipErrorInvalidValue;
+  if (tile_m == 256 && tile_n == 256 && rk == 64) return gemm_phase(d, 256, 256, splitk, partials, s, keep_partials);
   if (keep_partials && (!d.epi.out_f32 || d.epi.bias || d.epi.act != EPI_NONE || d.epi.drop.thr || d.epi.out2))
     return hipErrorInvalidValue;
   if (splitk < 1 || splitk > d.K / rk) return hipErrorInvalidValue;
@@ -503,14 +506,13 @@ hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int spli
   p.M = d.M; p.N = d.N; p.K = d.K;
   p.lda = d.lda; p.ldb = d.ldb;
   p.splitk = splitk;
-  p.tiles_m = d.M / tile_m; p.tiles_n = d.N / tile_n;
+  p.tiles_m = (d.M + tile_m - 1) / tile_m; p.tiles_n = d.N / tile_n;
   p.partials = partials;
   p.epi = d.epi;
   dim3 grid((unsigned)(p.tiles_m * p.tiles_n * splitk));
   hipError_t e;
   if (rk == 64) {
-    if (tile_m == 256 && tile_n == 256) e = ring::launch_layout<256, 256, 64>(d, p, grid, s);
-    else if (tile_m == 256) e = ring::launch_layout<256, 128, 64>(d, p, grid, s);
+    if (tile_m == 256) e = ring::launch_layout<256, 128, 64>(d, p, grid, s);
     else if (tile_n == 256) e = ring::launch_layout<128, 256, 64>(d, p, grid, s);
     else e = ring::launch_layout<128, 128, 64>(d, p, grid, s);
   } else {

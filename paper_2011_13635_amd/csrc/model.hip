@@ -160,7 +160,7 @@ struct mslt_model {
   // pinned host scalars
   int32_t* h_counters; float* h_loss;
   // last step
-  int few_div = 1;         // 2 while the forward of a step that belongs on two chains is queued as one (see `halves`)
+  int few_rows = 0;        // while the forward of a step that belongs on two chains is queued: rows of its first part (see `halves`)
   bool have_grads;
   int last_f, last_k, last_emb, last_B, last_S, last_M;
   const void* last_prefix;
@@ -695,33 +695,41 @@ static int layer_backward_end(mslt_model* m, int l) {
   return MSLT_OK;
 }
 
-// Tile shape and split factor of the large-tile kernel for one product, or false when the 128-wide
-// kernel should take it.  One workgroup occupies a compute unit, so what counts is how full the rounds
-// of 256 workgroups are: a 256x256 tile moves the fewest bytes per FLOP (relative rate 1), the two
-// half-size tiles about 0.88 of it (measured on the step's shapes), and splitting k costs the partial
-// sums and a second launch (factor 0.9).
-struct RingPlan { int tm, tn, rk, sk; };
-static bool ring_plan(const GemmDesc& d, bool allow_splitk, size_t partial_floats, RingPlan* out) {
-  static const int cand[3][2] = {{256, 256}, {128, 256}, {256, 128}};
-  const int rk = 64;
-  if (d.K % rk) return false;
-  double best = 0.0;
+// Tile of a product with a k-contiguous A for the large-tile kernels, or false when none takes it.  What counts is how
+// full the rounds of workgroups are (256 compute units; a 256x128 workgroup takes half of one) times what a tile shape
+// reaches when they are full, relative to 256x256.  The rates are those with which this rule agrees with the measured
+// order of the shapes, us:
+//                           256x256  256x384  256x128  128x256  128x192
+//   8192x4096x1024 GELU          70        -       73       96        -
+//   8192x3072x1024               52       44       51       60       68
+//   8192x1024x4096               79        -       69       63        -
+//   8192x3072x768 GELU           56       44       49       64       71
+//   8192x2304x768                37       31       36       41       40
+//   8192x768x3072                63       99       54       49       44
+//   5504x3072x768                37       30       36       37       37
+//   5504x2304x768                20       28       23       25       36
+//   4096x3072x768 GELU           26       38       27       31       30
+//   1280x30592x768                -        -       65       84        -
+// The data gradient (k-strided B) keeps the order: 8192x4096x1024 58 / - / 65 / 87 / -, 8192x3072x768 45 / 37 / 42 / 53 / 62,
+// 8192x768x3072 61 / 100 / 54 / 45 / 46.
+// 128x128 is the register-staged kernel, two workgroups on a compute unit: 128x30592x768 25 us, 256x128 tiles half of
+// which lie past the end 28.
+enum TileKernel { TILE_PHASE, TILE_RING, TILE_128 };
+struct TilePlan { TileKernel kernel; int tm, tn; double score; };
+static bool tile_plan(const GemmDesc& d, TilePlan* out) {
+  static const struct { TileKernel kernel; int tm, tn, slots; double rate; } cand[] = {
+      {TILE_PHASE, 256, 256, 256, 1.0},  {TILE_PHASE, 256, 384, 256, 0.9},  {TILE_PHASE, 256, 128, 512, 0.97},
+      {TILE_RING, 128, 256, 256, 0.62},  {TILE_PHASE, 128, 192, 256, 0.55}, {TILE_128, 128, 128, 512, 0.58}};
+  out->score = 0.0;
   for (auto& c : cand) {
-    if (!gemm_ring_supported(d, c[0], c[1], rk)) continue;
-    const int tiles = (d.M / c[0]) * (d.N / c[1]), nk = d.K / rk;
-    int sk = 1;
-    if (allow_splitk && tiles < 192) {
-      sk = 256 / tiles;
-      if (sk > 8) sk = 8;
-      if (sk > nk / 4) sk = nk / 4;
-      while (sk > 1 && (size_t)sk * d.M * d.N > partial_floats) --sk;
-      if (sk < 1) sk = 1;
-    }
-    const int wgs = tiles * sk, rounds = (wgs + 255) / 256;
-    double score = (c[0] == 256 && c[1] == 256 ? 1.0 : 0.88) * wgs / (rounds * 256.0) * (sk > 1 ? 0.9 : 1.0);
-    if (score > best) { best = score; *out = RingPlan{c[0], c[1], rk, sk}; }
+    const bool ok = c.kernel == TILE_PHASE  ? gemm_phase_supported(d, c.tm, c.tn)
+                    : c.kernel == TILE_RING ? gemm_ring_supported(d, c.tm, c.tn, 64, true) : gemm_mfma_supported(d);
+    if (!ok) continue;
+    const double tiles = (double)((d.M + c.tm - 1) / c.tm) * (d.N / c.tn);
+    const double score = c.rate * ((double)d.M * d.N / c.tm / c.tn) / (ceil(tiles / c.slots) * c.slots);
+    if (score > out->score) *out = TilePlan{c.kernel, c.tm, c.tn, score};
   }
-  return best > 0.0;
+  return out->score > 0.0;
 }
 
 // sum_later: the result is a parameter gradient nothing reads before the optimizer, so a split product may
@@ -732,21 +740,22 @@ static GemmPlace on_main(const mslt_model* m) { return GemmPlace{m->stream, m->s
 static int run_gemm(mslt_model* m, const GemmDesc& d, const GemmPlace& at, bool allow_splitk = false, bool sum_later = false) {
   const hipStream_t st = at.st;
   float* const partials = at.partials;
-  const bool use_mfma = m->mfma && gemm_mfma_supported(d);
+  const bool nt = d.a_kcontig && d.b_kcontig, tn = !d.a_kcontig && !d.b_kcontig;
+  // Which kernel takes which product was settled by measuring whole steps (two kernel chains run side by
+  // side there, so a kernel's footprint counts as much as its own speed): forward-type products (both
+  // operands k-contiguous) go to the large tiles, and so do data-gradient products (the weight k-strided) that keep
+  // at least a third of the chip's rate busy with them (BERT-Large 24 layers 32x512 44.6 -> 42.4 ms).  Smaller ones stay with
+  // the 128-wide register-staged kernel, which may split the contraction and leaves room on a compute unit for the
+  // weight gradients beside them (BERT-Base, first stage, 4096 rows: 1964 us, with 128x192 tiles 1999);
+  // weight-gradient products (both operands k-strided) that no grouped launch takes to 128x128 tiles, two workgroups per
+  // compute unit.  A product with too few tiles for either goes to the kernel that splits the contraction inside a workgroup.
+  TilePlan tp{};
+  const int few = m->mfma ? gemm_few_tile(d, m->few_rows ? m->few_rows : d.M) : 0;
+  const bool large = !few && m->mfma && gemm_rows_supported(d) && d.a_kcontig && tile_plan(d, &tp) && tp.kernel != TILE_128 && (nt || tp.score >= 0.33);
+  const bool use_mfma = few || large || (m->mfma && gemm_mfma_supported(d));
   const double out_esz = d.epi.out_f32 ? 4.0 : (double)m->esz;
   ProfScope ps(m, !use_mfma ? PC_GEMM_GUARDED : (d.a_kcontig ? (d.b_kcontig ? PC_GEMM_NT : PC_GEMM_NN) : PC_GEMM_TN),
                2.0 * d.M * d.N * d.K, ((double)d.M * d.K + (double)d.N * d.K) * m->esz + (double)d.M * d.N * out_esz);
-  // Which kernel takes which product was settled by measuring whole steps (two kernel chains run side by
-  // side there, so a kernel's footprint counts as much as its own speed): forward-type products (both
-  // operands k-contiguous) go to the large-tile kernel; weight-gradient products (both operands k-strided)
-  // to its 128x128 form, two workgroups per compute unit, fed by direct loads and transposing LDS reads;
-  // data-gradient products stay on the 128-wide register-staged kernel, except the one with a wide output (the
-  // gradient of the feed-forward layer's hidden activation), which gains on the large tiles in the step as well.
-  // A product with too few tiles for either goes to the kernel that splits the contraction inside a workgroup.
-  RingPlan rp;
-  const int few = use_mfma ? gemm_few_tile(d, d.M / m->few_div) : 0;
-  const bool nt = d.a_kcontig && d.b_kcontig, tn = !d.a_kcontig && !d.b_kcontig;
-  const bool nn_wide = d.a_kcontig && !d.b_kcontig && d.N >= 2048 && d.M >= 4096;
   if (few) {
     HIP_TRY(gemm_few(d, few, st));
   } else if (use_mfma && tn && gemm_ring_supported(d, 128, 128, 64)) {
@@ -762,8 +771,9 @@ static int run_gemm(mslt_model* m, const GemmDesc& d, const GemmPlace& at, bool 
       while (sk > 1 && (size_t)sk * d.M * d.N > m->splitk_floats) --sk;
       HIP_TRY(gemm_ring(d, 128, 128, 64, sk, partials, st));
     }
-  } else if (use_mfma && (nt || nn_wide) && ring_plan(d, allow_splitk, m->splitk_floats, &rp)) {
-    HIP_TRY(gemm_ring(d, rp.tm, rp.tn, rp.rk, rp.sk, partials, st));
+  } else if (large) {
+    if (tp.kernel == TILE_PHASE) HIP_TRY(gemm_phase(d, tp.tm, tp.tn, 1, nullptr, st));
+    else HIP_TRY(gemm_ring(d, tp.tm, tp.tn, 64, 1, nullptr, st));
   } else if (use_mfma) {
     int sk = allow_splitk ? pick_splitk(d.M, d.N, d.K) : 1;
     while (sk > 1 && (size_t)sk * d.M * d.N > m->splitk_floats) --sk;
@@ -878,6 +888,7 @@ static hipError_t attention_bwd(int dtype, const AttnBwdDesc& a, hipStream_t s) 
 // the stream.  Without a part the layer runs on all Tr rows on the main stream.
 struct FwdPart {
   int b0, nb;        // sequences [b0, b0 + nb)
+  int rows;          // token rows from b0 * S on (the last part takes the padded rows along)
   hipStream_t st;
 };
 static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, const void* Xin, void* Xout,
@@ -885,7 +896,7 @@ static int layer_forward(mslt_model* m, int l, const mslt_batch* bt, int Tr, con
   const int H = m->H, F = m->F, S = bt->seq;
   const int nb = part ? part->nb : bt->batch;
   const size_t r0 = part ? (size_t)part->b0 * S : 0;          // first token row
-  const int rows = part ? nb * S : Tr;
+  const int rows = part ? part->rows : Tr;
   hipStream_t s = part ? part->st : m->stream;
   // (two parts run side by side and are planned alike: neither has the scratch of the main stream)
   const GemmPlace place = part ? GemmPlace{part->st, nullptr} : on_main(m);
@@ -1153,7 +1164,7 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   m->later.clear();          // (a step that failed half-way may have left jobs behind)
   m->later_used = 0;
   m->later_on = m->lpg == 1;
-  m->few_div = 1;
+  m->few_rows = 0;
 
   // S0: batch check and compaction of the predicted positions (only index scratch is written)
   HIP_TRY(batch_scan(bt->input_ids, bt->token_type_ids, bt->attn_mask, bt->labels, T, m->V, m->cfg.type_vocab, m->cap,
@@ -1178,10 +1189,9 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   // The two halves of the batch go through the encoder as two independent chains of kernels, one per
   // stream: where a kernel of one chain leaves compute units idle (a last, partly filled round of
   // workgroups, its ramp-up and its drain) kernels of the other chain take them; four chains on four
-  // streams were slower.  Dropout indexes its decisions by position
-  // in the whole batch: the second half's kernels get keys that carry its offset (S even keeps the
-  // offset of the attention probabilities a multiple of 4).  Off while event profiling.
-  // (queued as one chain then, with the kernels the halves would take, so that the results are the same bits)
+  // streams were slower.  Dropout indexes its decisions by position in the whole batch: the second half's kernels get keys that
+  // carry its offset, which has to be a multiple of 4.  Off while event profiling
+  // (queued as one chain then, with the kernels the halves would take, so that the results are the same bits).
   // One chain where the widest product, a feed-forward one, has at most 2^30 operations: such a product lasts about as
   // long as its launch, and a second chain only doubles the launches the host has to queue.  Two chains / one, us:
   //   at the line and below (at most 2^30): 128-wide 2+1 layers 4x64 358 / 289, 32x64 368 / 331, 64x128 421 / 424; 256-wide
@@ -1190,11 +1200,12 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   //   3723 / 4228; Large 18+6 2x128 2554 / 2607, 8x128 3584 / 3763, 32x128 7359 / 7378; 256-wide 32x128 774 / 791.
   // 512-wide models from 1.5 to 8 times the line are the exception (one chain ahead by up to 4 %, 8x128 771 / 742): no
   // line by operations parts them from Base at 2x128.
-  const bool two_chains = m->dtype == 1 && m->mfma && B % 2 == 0 && (T / 2) % 128 == 0 && Tr == T && S % 2 == 0 &&
+  const int B1 = (B + 1) / 2, R1 = B1 * S;
+  const bool two_chains = m->dtype == 1 && m->mfma && B % 2 == 0 && R1 % 128 == 0 && Tr == T && S % 2 == 0 &&
                           (double)T * m->F * H > (double)(1 << 29);
   const bool halves = two_chains && !m->prof.on;
-  m->few_div = two_chains && !halves ? 2 : 1;
-  const FwdPart parts[2] = {{0, B / 2, s}, {B / 2, B / 2, m->side}};
+  m->few_rows = two_chains ? R1 : 0;
+  const FwdPart parts[2] = {{0, B1, R1, s}, {B1, B - B1, Tr - R1, m->side}};
   if (halves) {
     HIP_TRY(hipEventRecord(m->ev_fork, s));
     HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
@@ -1219,7 +1230,7 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
     x = m->stash[l - f].xout;
   }
   if (halves) RC(side_join(m));
-  m->few_div = 1;
+  m->few_rows = 0;
   HIP_TRY(hipEventSynchronize(m->ev_scan));
   // M: compacted rows (predicted positions, plus every first token when there is a next-sentence head);
   // Mn: those of them that carry a masked-LM label
@@ -1542,12 +1553,21 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
                   K, tile_m, tile_n, tile_k, splitk);
     HIP_TRY(gemm_ring(d, tile_m, tile_n, tile_k, splitk, (float*)partials, st));
   } else if (kernel == 3) {
-    if (!gemm_few_supported(d) || tile_m != tile_n || (tile_m != 32 && tile_m != 64) || splitk != 1)
+    if (!gemm_mfma_supported(d) || !gemm_few_supported(d) || tile_m != tile_n || (tile_m != 32 && tile_m != 64) || splitk != 1)
       return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d not taken by the few-tile kernel with tile %dx%d, splitk %d", M, N, K,
                   tile_m, tile_n, splitk);
     HIP_TRY(gemm_few(d, tile_m, st));
+  } else if (kernel == 5) {
+    const bool few = tile_m == tile_n && (tile_m == 32 || tile_m == 64), ring = tile_m == 128 && tile_n == 256;
+    if (splitk != 1 || tile_k != 64 || !d.a_kcontig ||
+        !(few ? gemm_few_supported(d) : ring ? gemm_ring_supported(d, 128, 256, 64, true) : gemm_phase_supported(d, tile_m, tile_n)))
+      return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d not taken for any row count with tile %dx%d, splitk %d", M, N, K, tile_m,
+                  tile_n, splitk);
+    if (few) HIP_TRY(gemm_few(d, tile_m, st));
+    else if (ring) HIP_TRY(gemm_ring(d, 128, 256, 64, 1, nullptr, st));
+    else HIP_TRY(gemm_phase(d, tile_m, tile_n, 1, nullptr, st));
   } else {
-    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 4");
+    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 5");
   }
   return MSLT_OK;
 }
