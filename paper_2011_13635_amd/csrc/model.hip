@@ -1189,7 +1189,8 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   // The two halves of the batch go through the encoder as two independent chains of kernels, one per
   // stream: where a kernel of one chain leaves compute units idle (a last, partly filled round of
   // workgroups, its ramp-up and its drain) kernels of the other chain take them; four chains on four
-  // streams were slower.  Dropout indexes its decisions by position in the whole batch: the second half's kernels get keys that
+  // streams were slower.  The halves meet at a sequence, at any row: the products of the first one leave the rows of the
+  // second alone.  Dropout indexes its decisions by position in the whole batch: the second half's kernels get keys that
   // carry its offset, which has to be a multiple of 4.  Off while event profiling
   // (queued as one chain then, with the kernels the halves would take, so that the results are the same bits).
   // One chain where the widest product, a feed-forward one, has at most 2^30 operations: such a product lasts about as
@@ -1198,10 +1199,12 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
   //   4+2 2x128 573 / 519, 16x128 650 / 629; 512-wide 4+2 4x128 650 / 625;
   //   above it: Base 9+3 2x128 (1.1 * 2^30) 1152 / 1170, 4x128 1274 / 1325, 8x128 1504 / 1611, 16x128 1866 / 1886, 64x128
   //   3723 / 4228; Large 18+6 2x128 2554 / 2607, 8x128 3584 / 3763, 32x128 7359 / 7378; 256-wide 32x128 774 / 791.
+  //   unequal halves: Base 9+3 3x128 1258 / 1346, 5x128 1416 / 1402, 11x128 1674 / 1776, 33x100 2517 / 2764, 27x203 with dropout
+  //   3469 / 3930; Large 18+6 3x128 3000 / 3245, 13x200 with dropout 6530 / 7170, 45x200 12510 / 14830 (one chain: the kernels before).
   // 512-wide models from 1.5 to 8 times the line are the exception (one chain ahead by up to 4 %, 8x128 771 / 742): no
   // line by operations parts them from Base at 2x128.
   const int B1 = (B + 1) / 2, R1 = B1 * S;
-  const bool two_chains = m->dtype == 1 && m->mfma && B % 2 == 0 && R1 % 128 == 0 && Tr == T && S % 2 == 0 &&
+  const bool two_chains = m->dtype == 1 && m->mfma && B >= 2 && (!m->drop_thr || (long long)R1 * m->nh * S % 4 == 0) &&
                           (double)T * m->F * H > (double)(1 << 29);
   const bool halves = two_chains && !m->prof.on;
   m->few_rows = two_chains ? R1 : 0;

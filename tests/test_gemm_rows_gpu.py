@@ -1,8 +1,9 @@
 """Tiles of a matrix product whose rows are no multiple of the tile: the right result in every row, none past the end
-written, none past the end of A read (its buffer ends there)."""
+written, none past the end of A read (its buffer ends there); and a step whose two forward chains meet inside a tile."""
+import numpy as np
 import pytest
 
-from paper_2011_13635_amd import binding
+from paper_2011_13635_amd import binding, synth
 from test_gemm_gpu import _operands
 
 pytestmark = pytest.mark.gpu
@@ -24,3 +25,25 @@ def test_any_row_count(tm, tn, bkc, M, K):
         assert torch.equal(c[:M].cpu(), want)
         assert bool(torch.isnan(c[M:]).all())
 
+
+@pytest.mark.parametrize("B,S,dropout", [(27, 203, 0.1), (9, 128, 0.0), (3, 510, 0.1)])
+def test_chains_of_unequal_halves_give_the_bits_of_one_chain(B, S, dropout):
+    import torch
+    shape = synth.bert_base_shape(2)
+    W = synth.pack_weights(shape, synth.make_weights(shape, seed=11))
+    batch = synth.make_batch(shape, B, S, seed=12, ragged=True)
+    m = binding.Model(binding.make_config(shape, B, S, 1))
+    m.mslt_load_params(W)
+    bt = m.device_batch(batch)
+    out = []
+    for one_chain in (False, True, False):
+        m.mslt_profile_enable(one_chain)
+        if dropout:
+            m.mslt_set_dropout(dropout, 3, 0)
+        loss = m.mslt_stage_step(1, 1, False, bt)
+        out.append((loss, m.mslt_debug_prefix_output(B, S), m.mslt_get_grads()))
+    m.close()
+    for o in out[1:]:
+        assert o[0] == out[0][0]
+        assert np.array_equal(o[1], out[0][1])
+        assert np.array_equal(o[2], out[0][2])
