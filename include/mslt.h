@@ -237,7 +237,7 @@ int mslt_profile_read(mslt_model* m, mslt_profile_entry* out, int cap, int* n);
 /* Test and measurement aid for the matrix products the step is made of (Sections 3.1 and 3.2 name
  * the layers; their linear maps are these products): C[M,N] = sum_k A(m,k) B(n,k) on DEVICE operands
  * through one chosen kernel, enqueued on hip_stream (hipStream_t as void*, null = default stream).
- * A and B are bf16 (but for kernel 4; 2 bytes per element, round to nearest even); a_kcontig != 0: A(m,k) = A[m*K + k],
+ * A and B are bf16 (but for kernels 4 and 6; 2 bytes per element, round to nearest even); a_kcontig != 0: A(m,k) = A[m*K + k],
  * else A[k*M + m]; the same for B with n and N.  C is row-major [M,N], bf16, or fp32 when out_f32 != 0.
  * kernel 0: guarded kernel (any shape); kernel 4: the same on fp32 operands, out_f32 != 0.  kernel 1: 128-wide MFMA kernel, tile_m 0 (chosen by
  * shape), 128 or 256; M % 128 == 0, N % 128 == 0, K % 64 == 0.  kernel 2: large-tile kernel fed by
@@ -245,7 +245,8 @@ int mslt_profile_read(mslt_model* m, mslt_profile_entry* out, int cap, int* n);
  * tile_k 64 (or 32, not for 128x128); M % tile_m == 0, N % tile_n == 0, K % tile_k == 0.  kernel 3:
  * few-tile kernel, a_kcontig != 0, sizes as kernel 1, tile_m = tile_n = 32 or 64.  kernel 5: the tiles a step uses where
  * the rows of C are no multiple of the tile, a_kcontig != 0, any M, N % tile_n == 0 (128 at least), K % 64 == 0: 256x256,
- * 256x384, 256x128, 128x256, 128x192, 64x64 or 32x32.  splitk > 1 (not kernels 3 and 5) splits the contraction over
+ * 256x384, 256x128, 128x256, 128x192, 64x64 or 32x32.  kernel 6: fp32 kernel of the step, fp32 operands, out_f32 != 0,
+ * rows of a multiple of 16 bytes.  splitk > 1 (not kernels 3 and 5) splits the contraction over
  * workgroups and needs `partials`, DEVICE scratch of at least splitk*M*N*4 bytes (partial_bytes says how large it is).  Returns MSLT_ERR_ARG for a shape or
  * choice the kernel does not take; nothing is enqueued then.  Does not block. */
 int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, void* C, int M, int N, int K, int a_kcontig,

@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libmslt.so")
-SOURCES = ["model.hip", "rowwise.hip", "gemm_guarded.hip", "gemm_mfma.hip", "gemm_ring.hip", "gemm_phase.hip", "gemm_few.hip",
+SOURCES = ["model.hip", "rowwise.hip", "gemm_guarded.hip", "gemm_f32.hip", "gemm_mfma.hip", "gemm_ring.hip", "gemm_phase.hip", "gemm_few.hip",
            "attention_simple.hip", "attention_mfma.hip", "attention_f32.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-result"]

@@ -154,6 +154,11 @@ struct GemmDesc {
 // gives the factor for a product when that many floats are available.
 int guarded_splitk(int M, int N, int K, int dtype, size_t partial_floats);
 hipError_t gemm_guarded(int dtype, const GemmDesc& d, int splitk, float* partials, hipStream_t s);
+hipError_t guarded_reduce_f32(const float* partials, int splitk, int M, int N, const Epilogue& e, hipStream_t s);
+// fp32 kernel for operands with 16-byte aligned rows (K % 4 == 0 where one is k-contiguous); partials as above.
+bool gemm_f32_supported(const GemmDesc& d);
+int f32_splitk(int M, int N, int K, size_t partial_floats);
+hipError_t gemm_f32(const GemmDesc& d, int splitk, float* partials, hipStream_t s);
 // MFMA kernel (bf16 only): M, N multiples of 128, K multiple of 64 (per split), all loads in
 // bounds by construction (padded buffers).  splitk > 1 writes fp32 partials to `partials`
 // ([splitk][M][N]) and reduces them in fixed order into the epilogue.

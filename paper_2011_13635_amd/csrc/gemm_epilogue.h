@@ -102,6 +102,36 @@ static __device__ __forceinline__ void epilogue8(const Epilogue& e, int m, int n
   }
 }
 
+// ---- epilogue on one element (activation type AT) -----------------------------------------------
+// v: accumulator + bias; x: the stored GELU derivative, the addend, or (accumulate) what the output holds
+template <typename AT>
+static __device__ __forceinline__ void finish_one(const Epilogue& e, int m, int n, float v, float x) {
+  if (e.drop.thr) v *= drop_factor(e.drop, (uint64_t)m * e.drop_ld + n);
+  const size_t o = (size_t)m * e.ldo + n;
+  if (e.act == EPI_GELU) {
+    float g;
+    gelu_both_f(v, v, g);
+    if (e.out2) st_dgelu(reinterpret_cast<AT*>(e.out2) + o, g);
+  } else if (e.act == EPI_MUL) {
+    v *= x;
+  } else if (e.act == EPI_ADD) {
+    v += x;
+  }
+  if (e.out_f32) {
+    float* p = reinterpret_cast<float*>(e.out) + o;
+    *p = e.accumulate ? *p + v : v;
+  } else {
+    stf(reinterpret_cast<AT*>(e.out) + o, v);
+  }
+}
+template <typename AT>
+static __device__ __forceinline__ float load_aux(const Epilogue& e, int m, int n) {
+  const size_t o = (size_t)m * e.ldaux + n;
+  if (e.act == EPI_MUL) return ld_dgelu(reinterpret_cast<const AT*>(e.aux) + o);
+  if (e.act == EPI_ADD) return e.aux_f32 ? reinterpret_cast<const float*>(e.aux)[o] : ldf(reinterpret_cast<const AT*>(e.aux) + o);
+  return 0.f;
+}
+
 // sums the split-k partials [splitk][M][N] in split order and applies the epilogue (defined with the 128-wide kernel)
 __global__ void k_splitk_reduce(const float* __restrict__ partials, int splitk, int M, int N, Epilogue e);
 

@@ -1,5 +1,5 @@
 // Guarded matrix-core GEMM: C(m,n) = sum_k A(m,k) B(n,k) with the shared epilogue, any shape, any leading
-// dimension, fp32 accumulation.  It is the GEMM of fp32 mode (v_mfma_f32_32x32x2_f32) and takes the bf16
+// dimension, fp32 accumulation.  It takes the fp32 products that gemm_f32.hip does not (v_mfma_f32_32x32x2_f32) and the bf16
 // products whose sizes the 128-wide kernels do not fit (v_mfma_f32_32x32x16_bf16: next-sentence head, hidden
 // sizes that are no multiple of 128).
 //
@@ -28,35 +28,6 @@ namespace mslt {
 namespace guarded {
 
 constexpr int TILE = 64, SLAB_BYTES = 128, OPERAND_BYTES = TILE * SLAB_BYTES;
-
-// v: accumulator + bias; x: the stored GELU derivative, the addend, or (accumulate) what the output holds
-template <typename AT>
-__device__ __forceinline__ void finish_one(const Epilogue& e, int m, int n, float v, float x) {
-  if (e.drop.thr) v *= drop_factor(e.drop, (uint64_t)m * e.drop_ld + n);
-  const size_t o = (size_t)m * e.ldo + n;
-  if (e.act == EPI_GELU) {
-    float g;
-    gelu_both_f(v, v, g);
-    if (e.out2) st_dgelu(reinterpret_cast<AT*>(e.out2) + o, g);
-  } else if (e.act == EPI_MUL) {
-    v *= x;
-  } else if (e.act == EPI_ADD) {
-    v += x;
-  }
-  if (e.out_f32) {
-    float* p = reinterpret_cast<float*>(e.out) + o;
-    *p = e.accumulate ? *p + v : v;
-  } else {
-    stf(reinterpret_cast<AT*>(e.out) + o, v);
-  }
-}
-template <typename AT>
-__device__ __forceinline__ float load_aux(const Epilogue& e, int m, int n) {
-  const size_t o = (size_t)m * e.ldaux + n;
-  if (e.act == EPI_MUL) return ld_dgelu(reinterpret_cast<const AT*>(e.aux) + o);
-  if (e.act == EPI_ADD) return e.aux_f32 ? reinterpret_cast<const float*>(e.aux)[o] : ldf(reinterpret_cast<const AT*>(e.aux) + o);
-  return 0.f;
-}
 
 // One operand's slab: two 16-byte chunks per thread.
 //   k-contiguous: chunk tid%8 of row tid/8 + 32 i;   k-strided: E = 16/sizeof(AT) rows of k number tid/(64/E) + i*BK/2
@@ -236,6 +207,11 @@ int guarded_splitk(int M, int N, int K, int dtype, size_t partial_floats) {
     if (s == 1 || t < best) { best = t; pick = s; }
   }
   return pick;
+}
+
+hipError_t guarded_reduce_f32(const float* partials, int splitk, int M, int N, const Epilogue& e, hipStream_t s) {
+  guarded::k_guarded_reduce<float><<<dim3((unsigned)(((size_t)M * N + 255) / 256)), dim3(256), 0, s>>>(partials, splitk, M, N, e);
+  return hipGetLastError();
 }
 
 hipError_t gemm_guarded(int dtype, const GemmDesc& d, int splitk, float* partials, hipStream_t s) {

@@ -778,6 +778,8 @@ static int run_gemm(mslt_model* m, const GemmDesc& d, const GemmPlace& at, bool 
     int sk = allow_splitk ? pick_splitk(d.M, d.N, d.K) : 1;
     while (sk > 1 && (size_t)sk * d.M * d.N > m->splitk_floats) --sk;
     HIP_TRY(gemm_mfma(d, sk, partials, st));
+  } else if (m->dtype == 0 && gemm_f32_supported(d)) {
+    HIP_TRY(gemm_f32(d, partials ? f32_splitk(d.M, d.N, d.K, m->splitk_floats) : 1, partials, st));
   } else {
     const int sk = partials ? guarded_splitk(d.M, d.N, d.K, m->dtype, m->splitk_floats) : 1;
     HIP_TRY(gemm_guarded(m->dtype, d, sk, partials, st));
@@ -1569,8 +1571,12 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
     if (few) HIP_TRY(gemm_few(d, tile_m, st));
     else if (ring) HIP_TRY(gemm_ring(d, 128, 256, 64, 1, nullptr, st));
     else HIP_TRY(gemm_phase(d, tile_m, tile_n, 1, nullptr, st));
+  } else if (kernel == 6) {
+    if (!out_f32 || !gemm_f32_supported(d) || splitk > (K + 31) / 32)
+      return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d, splitk %d not taken by the fp32 kernel", M, N, K, splitk);
+    HIP_TRY(gemm_f32(d, splitk, (float*)partials, st));
   } else {
-    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 5");
+    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 6");
   }
   return MSLT_OK;
 }
