@@ -363,6 +363,7 @@ struct OptHyper {
   const float* gate = nullptr;
 };
 constexpr int OPT_CHUNK = 16384;  // elements per workgroup
+constexpr int OPT_THREADS = 1024;
 // Updates tensors [tensor0, tensor0+n_tensors), whose chunks are [chunk0, chunk0+n_chunks).
 // tsteps[i] is tensor i's step count (already incremented for this update).
 // chunk_norms: 2 floats per chunk; ratio: 1 float per tensor (LAMB only).
