@@ -328,8 +328,8 @@ def main():
                                "batch 64 x seq 128, LAMB (lr 0.00088), bf16 with fp32 master", "frozen_layers": f,
                    "trainable_layers": k, "batch": B, "seq_len": S, "tokens_per_step": tokens,
                    "predicted_per_step": int(len(batches[0]["masked_positions"])), "loss": round(float(loss), 5)},
-        "roofline": {"bound": "mfma", "kernel": "bf16 MFMA GEMM (k_gemm_ring for forward-type and weight-gradient "
-                     "products, k_gemm_mfma for data-gradient products, k_gemm_few for products of few tiles)", "achieved": round(achieved, 1),
+        "roofline": {"bound": "mfma", "kernel": "bf16 MFMA GEMM (k_gemm_phase, k_gemm_wide, k_gemm_pair, k_gemm_slim and k_gemm_ring for large "
+                     "products, k_gemm_mfma for split data gradients, k_gemm_few for products of few tiles)", "achieved": round(achieved, 1),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                      "traffic": recorded_gemm_traffic(), "traffic_unit": "bytes per launch (L2-miss side, FETCH_SIZE + "
                      "WRITE_SIZE scaled by a 256 MiB copy)", "algorithmic_bytes_per_launch":

@@ -21,10 +21,10 @@ import re
 import sys
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
-KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("gemm_ring.hip", "gemm_mfma.hip", "gemm_few.hip", "gemm_epilogue.h",
+KERNEL_SOURCES = [os.path.join(CSRC, f) for f in ("gemm_phase.hip", "gemm_ring.hip", "gemm_mfma.hip", "gemm_few.hip", "gemm_epilogue.h",
                                                   "common.h")]
 ROWWISE_SOURCES = [os.path.join(CSRC, f) for f in ("rowwise.hip", "attention_mfma.hip", "common.h")]
-GEMM_KERNELS = ("k_gemm_mfma", "k_gemm_ring", "k_gemm_few")
+GEMM_KERNELS = ("k_gemm_phase", "k_gemm_wide", "k_gemm_pair", "k_gemm_slim", "k_gemm_mfma", "k_gemm_ring", "k_gemm_few")
 COPY_BYTES = 256 * 1024 * 1024
 
 
