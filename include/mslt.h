@@ -253,6 +253,12 @@ int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, void* C, int
                     int b_kcontig, int out_f32, int kernel, int tile_m, int tile_n, int tile_k, int splitk,
                     void* partials, size_t partial_bytes);
 
+/* Which of those kernels a step takes for a product of these sizes, and how: *kernel as above, its tile (0 where the kernel
+ * chooses) and the number of parts of the contraction (for weight gradients before the scratch at hand is looked at).
+ * precision as in mslt_config, rows of the operands without gaps and aligned.  Host only: no GPU is needed. */
+int mslt_debug_plan_gemm(int precision, int M, int N, int K, int a_kcontig, int b_kcontig, int out_f32, int* kernel, int* tile_m,
+                         int* tile_n, int* splitk);
+
 /* Test aid for the attention of one layer (Section 4.1, the architecture of BERT) through the kernels a step takes for
  * these sizes, forward and, when dctx is not null, backward, on DEVICE operands, enqueued on hip_stream.  precision as
  * in mslt_config: 0 fp32, 1 bf16 (qkv, ctx, dctx, dqkv).  qkv [batch*seq, 3H]: Q | K | V, head h at columns

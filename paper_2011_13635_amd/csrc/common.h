@@ -158,6 +158,8 @@ hipError_t guarded_reduce_f32(const float* partials, int splitk, int M, int N, c
 // fp32 kernel for operands with 16-byte aligned rows (K % 4 == 0 where one is k-contiguous); partials as above.
 bool gemm_f32_supported(const GemmDesc& d);
 int f32_splitk(int M, int N, int K, size_t partial_floats);
+// whether it should take a product with this split rather than the guarded kernel with its own
+bool gemm_f32_pays(const GemmDesc& d, int splitk, int guarded_splitk);
 hipError_t gemm_f32(const GemmDesc& d, int splitk, float* partials, hipStream_t s);
 // MFMA kernel (bf16 only): M, N multiples of 128, K multiple of 64 (per split), all loads in
 // bounds by construction (padded buffers).  splitk > 1 writes fp32 partials to `partials`

@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(512, 4) k_gemm_f32(GemmDesc d, int tiles_m, in
     a.issue((lo + i) * BK, d.K, i < n, w, smem + slot);
     b.issue((lo + i) * BK, d.K, i < n, w, smem + slot + OPERAND);
   };
-  // The group's first slabs: 0, 2 and 4 or 1 and 3.  From then on it queues slab i + 4 (slot (i - 1) % SLOTS, which the
+  // The group's first slabs: 0 and 2 or 1 and 3.  From then on it queues slab i + 4 (slot (i - 1) % SLOTS, which the
   // other group has read) when it reads slab i; the next one it reads has landed when four loads are in flight.
   for (int i = group; i < SLOTS - 1; i += 2) issue(i, i * SLOT);
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(4, 15));
@@ -218,6 +218,19 @@ int f32_splitk(int M, int N, int K, size_t partial_floats) {
     if (s == 1 || t < best) { best = t; pick = s; }
   }
   return pick;
+}
+
+// Where the guarded kernel is the faster one.  512 workgroups of this kernel are resident (80 KB of LDS each) and five or
+// more of the guarded one to a compute unit; a workgroup here starts with a ring to fill and ends with two sums to add.  So many
+// tiles of a short contraction run longer here, and so do parts of a split that hold a few slabs or start a second round.
+// This kernel / guarded, us: 3072x768, contraction 32 13.7 / 9.3, 128 17.5 / 15.5, 256 24.7 / 23.6, 304 (30592x768) 179 / 162,
+// 384 32 / 32; 30592x768x20 77 / 44; 2304x768x32 (432 tiles) 9.6 / 8.2; in parts, 256x768x768 in five 12.6 / 11.5,
+// 128x128x512 in four 8.9 / 8.5, 4x768x30592 in 64 51 / 41.  On the other side: 2304x768x128 11.8 / 12.3, 768x768x128 7.9 / 8.6,
+// 1536x512x2048 43 / 57 (the guarded rule leaves it whole).
+bool gemm_f32_pays(const GemmDesc& d, int splitk, int guarded_splitk) {
+  const int tiles = ((d.M + f32::TILE - 1) / f32::TILE) * ((d.N + f32::TILE - 1) / f32::TILE), slabs = (d.K + f32::BK - 1) / f32::BK;
+  if (splitk == 1) return !(tiles > 512 && slabs <= 10) && !(tiles > 384 && slabs == 1);
+  return splitk != guarded_splitk || ((long long)tiles * splitk <= 512 && (slabs + splitk - 1) / splitk > 5);
 }
 
 hipError_t gemm_f32(const GemmDesc& d, int splitk, float* partials, hipStream_t s) {

@@ -46,6 +46,8 @@ static const char* kProfNames[PC_COUNT] = {"gemm_mfma_nt", "gemm_mfma_nn", "gemm
                                            "attention_bwd", "layernorm_fwd", "layernorm_bwd", "bias_colsum", "embed_fwd",
                                            "head_gather_scatter", "cross_entropy", "embed_bwd", "optimizer", "gradient_sums"};
 static int pick_splitk(int M, int N, int K);
+// floats of scratch for partial sums: as many tiles as split products have at most
+static size_t splitk_scratch(bool mfma) { return (size_t)1024 * (mfma ? 128 * 128 : 64 * 64); }
 // Tile of the grouped weight-gradient launch of one layer (index into kGroupTile), or -1 when the products go
 // out one by one.  cnt[c]: tiles of all the products together at shape c; ok[c]: every product fits shape c.
 // 256x256 moves half the bytes per FLOP of 128x128 and 256x128 three quarters, but one such workgroup fills a
@@ -369,7 +371,7 @@ static size_t carve(mslt_model* m, char* base) {
   if (ct > red) red = ct;
   m->red_floats = red;
   m->red_scratch = b.take<float>(red * 4);
-  m->splitk_floats = (size_t)1024 * (m->mfma ? 128 * 128 : 64 * 64);   // as many tiles as split products have at most
+  m->splitk_floats = splitk_scratch(m->mfma);
   m->splitk = b.take<float>(m->splitk_floats * 4);
   m->splitk2 = b.take<float>(m->splitk_floats * 4);
   m->red2 = b.take<float>(red * 4);
@@ -732,6 +734,43 @@ static bool tile_plan(const GemmDesc& d, TilePlan* out) {
   return out->score > 0.0;
 }
 
+// Which kernel takes a product, with its tile and split; kernels are numbered as in mslt_debug_gemm.  (The tiles for any
+// row count are those of gemm_phase.hip and the 128x256 one of gemm_ring.hip.)
+enum GemmKernel { GK_GUARDED = 0, GK_128 = 1, GK_RING = 2, GK_FEW = 3, GK_GUARDED_F32 = 4, GK_ROWS = 5, GK_F32 = 6 };
+struct GemmPlan { GemmKernel kernel; int tm, tn, splitk; };
+// few_rows: rows by which the few-tile line is drawn (0: d.M).  floats: scratch for partial sums, 0 where there is none.
+// Which kernel takes which product was settled by measuring whole steps (two kernel chains run side by
+// side there, so a kernel's footprint counts as much as its own speed): forward-type products (both
+// operands k-contiguous) go to the large tiles, and so do data-gradient products (the weight k-strided) that keep
+// at least a third of the chip's rate busy with them (BERT-Large 24 layers 32x512 44.6 -> 42.4 ms).  Smaller ones stay with
+// the 128-wide register-staged kernel, which may split the contraction and leaves room on a compute unit for the
+// weight gradients beside them (BERT-Base, first stage, 4096 rows: 1964 us, with 128x192 tiles 1999);
+// weight-gradient products (both operands k-strided) that no grouped launch takes to 128x128 tiles, two workgroups per
+// compute unit.  A product with too few tiles for either goes to the kernel that splits the contraction inside a workgroup.
+static GemmPlan plan_gemm(bool mfma, int dtype, const GemmDesc& d, int few_rows, size_t floats, bool allow_splitk) {
+  const bool nt = d.a_kcontig && d.b_kcontig, tn = !d.a_kcontig && !d.b_kcontig;
+  auto fitting = [&](int sk) {
+    while (sk > 1 && (size_t)sk * d.M * d.N > floats) --sk;
+    return sk;
+  };
+  if (mfma) {
+    if (const int few = gemm_few_tile(d, few_rows ? few_rows : d.M)) return {GK_FEW, few, few, 1};
+    // (its scratch may be that of the step's last launch, which has room for every split)
+    if (tn && gemm_mfma_supported(d) && gemm_ring_supported(d, 128, 128, 64))
+      return {GK_RING, 128, 128, allow_splitk ? pick_splitk(d.M, d.N, d.K) : 1};
+    TilePlan tp{};
+    if (gemm_rows_supported(d) && d.a_kcontig && tile_plan(d, &tp) && tp.kernel != TILE_128 && (nt || tp.score >= 0.33))
+      return {GK_ROWS, tp.tm, tp.tn, 1};
+    if (gemm_mfma_supported(d)) return {GK_128, 0, 0, fitting(allow_splitk ? pick_splitk(d.M, d.N, d.K) : 1)};
+  }
+  const int sk = floats ? guarded_splitk(d.M, d.N, d.K, dtype, floats) : 1;
+  if (dtype == 0 && gemm_f32_supported(d)) {
+    const int sk32 = floats ? f32_splitk(d.M, d.N, d.K, floats) : 1;
+    if (gemm_f32_pays(d, sk32, sk)) return {GK_F32, 64, 64, sk32};
+  }
+  return {dtype ? GK_GUARDED : GK_GUARDED_F32, 64, 64, sk};
+}
+
 // sum_later: the result is a parameter gradient nothing reads before the optimizer, so a split product may
 // leave its partial sums for the batch at the end of the step
 // at: the stream and that stream's scratch for partial sums, null where there is none (a chain beside the main one)
@@ -740,49 +779,36 @@ static GemmPlace on_main(const mslt_model* m) { return GemmPlace{m->stream, m->s
 static int run_gemm(mslt_model* m, const GemmDesc& d, const GemmPlace& at, bool allow_splitk = false, bool sum_later = false) {
   const hipStream_t st = at.st;
   float* const partials = at.partials;
-  const bool nt = d.a_kcontig && d.b_kcontig, tn = !d.a_kcontig && !d.b_kcontig;
-  // Which kernel takes which product was settled by measuring whole steps (two kernel chains run side by
-  // side there, so a kernel's footprint counts as much as its own speed): forward-type products (both
-  // operands k-contiguous) go to the large tiles, and so do data-gradient products (the weight k-strided) that keep
-  // at least a third of the chip's rate busy with them (BERT-Large 24 layers 32x512 44.6 -> 42.4 ms).  Smaller ones stay with
-  // the 128-wide register-staged kernel, which may split the contraction and leaves room on a compute unit for the
-  // weight gradients beside them (BERT-Base, first stage, 4096 rows: 1964 us, with 128x192 tiles 1999);
-  // weight-gradient products (both operands k-strided) that no grouped launch takes to 128x128 tiles, two workgroups per
-  // compute unit.  A product with too few tiles for either goes to the kernel that splits the contraction inside a workgroup.
-  TilePlan tp{};
-  const int few = m->mfma ? gemm_few_tile(d, m->few_rows ? m->few_rows : d.M) : 0;
-  const bool large = !few && m->mfma && gemm_rows_supported(d) && d.a_kcontig && tile_plan(d, &tp) && tp.kernel != TILE_128 && (nt || tp.score >= 0.33);
-  const bool use_mfma = few || large || (m->mfma && gemm_mfma_supported(d));
+  const GemmPlan p = plan_gemm(m->mfma, m->dtype, d, m->few_rows, partials ? m->splitk_floats : 0, allow_splitk);
+  const bool guarded = p.kernel == GK_GUARDED || p.kernel == GK_GUARDED_F32 || p.kernel == GK_F32;
   const double out_esz = d.epi.out_f32 ? 4.0 : (double)m->esz;
-  ProfScope ps(m, !use_mfma ? PC_GEMM_GUARDED : (d.a_kcontig ? (d.b_kcontig ? PC_GEMM_NT : PC_GEMM_NN) : PC_GEMM_TN),
+  ProfScope ps(m, guarded ? PC_GEMM_GUARDED : (d.a_kcontig ? (d.b_kcontig ? PC_GEMM_NT : PC_GEMM_NN) : PC_GEMM_TN),
                2.0 * d.M * d.N * d.K, ((double)d.M * d.K + (double)d.N * d.K) * m->esz + (double)d.M * d.N * out_esz);
-  if (few) {
-    HIP_TRY(gemm_few(d, few, st));
-  } else if (use_mfma && tn && gemm_ring_supported(d, 128, 128, 64)) {
-    int sk = allow_splitk ? pick_splitk(d.M, d.N, d.K) : 1;
-    float* kept = nullptr;
-    if (sk > 1 && sum_later && d.epi.out_f32 && d.epi.ldo == d.N && !d.epi.bias && d.epi.act == EPI_NONE && !d.epi.drop.thr &&
-        !d.epi.out2)
-      kept = later_take(m, (size_t)sk * d.M * d.N);
-    if (kept) {
-      HIP_TRY(gemm_ring(d, 128, 128, 64, sk, kept, st, true));
-      m->later.push_back(reduce_job(kept, (float*)d.epi.out, sk, (size_t)d.M * d.N, d.epi.accumulate != 0, true));
-    } else {
-      while (sk > 1 && (size_t)sk * d.M * d.N > m->splitk_floats) --sk;
-      HIP_TRY(gemm_ring(d, 128, 128, 64, sk, partials, st));
+  switch (p.kernel) {
+    case GK_FEW: HIP_TRY(gemm_few(d, p.tm, st)); break;
+    case GK_RING: {
+      int sk = p.splitk;
+      float* kept = nullptr;
+      if (sk > 1 && sum_later && d.epi.out_f32 && d.epi.ldo == d.N && !d.epi.bias && d.epi.act == EPI_NONE && !d.epi.drop.thr &&
+          !d.epi.out2)
+        kept = later_take(m, (size_t)sk * d.M * d.N);
+      if (kept) {
+        HIP_TRY(gemm_ring(d, 128, 128, 64, sk, kept, st, true));
+        m->later.push_back(reduce_job(kept, (float*)d.epi.out, sk, (size_t)d.M * d.N, d.epi.accumulate != 0, true));
+      } else {
+        while (sk > 1 && (size_t)sk * d.M * d.N > m->splitk_floats) --sk;
+        HIP_TRY(gemm_ring(d, 128, 128, 64, sk, partials, st));
+      }
+      break;
     }
-  } else if (large) {
-    if (tp.kernel == TILE_PHASE) HIP_TRY(gemm_phase(d, tp.tm, tp.tn, 1, nullptr, st));
-    else HIP_TRY(gemm_ring(d, tp.tm, tp.tn, 64, 1, nullptr, st));
-  } else if (use_mfma) {
-    int sk = allow_splitk ? pick_splitk(d.M, d.N, d.K) : 1;
-    while (sk > 1 && (size_t)sk * d.M * d.N > m->splitk_floats) --sk;
-    HIP_TRY(gemm_mfma(d, sk, partials, st));
-  } else if (m->dtype == 0 && gemm_f32_supported(d)) {
-    HIP_TRY(gemm_f32(d, partials ? f32_splitk(d.M, d.N, d.K, m->splitk_floats) : 1, partials, st));
-  } else {
-    const int sk = partials ? guarded_splitk(d.M, d.N, d.K, m->dtype, m->splitk_floats) : 1;
-    HIP_TRY(gemm_guarded(m->dtype, d, sk, partials, st));
+    case GK_ROWS:
+      if (p.tm == 128 && p.tn == 256) HIP_TRY(gemm_ring(d, 128, 256, 64, 1, nullptr, st));
+      else HIP_TRY(gemm_phase(d, p.tm, p.tn, 1, nullptr, st));
+      break;
+    case GK_128: HIP_TRY(gemm_mfma(d, p.splitk, partials, st)); break;
+    case GK_F32: HIP_TRY(gemm_f32(d, p.splitk, partials, st)); break;
+    case GK_GUARDED:
+    case GK_GUARDED_F32: HIP_TRY(gemm_guarded(m->dtype, d, p.splitk, partials, st)); break;
   }
   return MSLT_OK;
 }
@@ -1578,6 +1604,21 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
   } else {
     return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 6");
   }
+  return MSLT_OK;
+}
+
+extern "C" int mslt_debug_plan_gemm(int precision, int M, int N, int K, int a_kcontig, int b_kcontig, int out_f32, int* kernel,
+                                    int* tile_m, int* tile_n, int* splitk) {
+  if (!kernel || !tile_m || !tile_n || !splitk) return fail(MSLT_ERR_ARG, "debug_plan_gemm: null output");
+  if (M < 1 || N < 1 || K < 1 || (precision != 0 && precision != 1)) return fail(MSLT_ERR_ARG, "debug_plan_gemm: bad size or precision");
+  GemmDesc d;
+  d.M = M; d.N = N; d.K = K;
+  d.a_kcontig = a_kcontig != 0; d.b_kcontig = b_kcontig != 0;
+  d.lda = d.a_kcontig ? K : M; d.ldb = d.b_kcontig ? K : N;
+  d.epi.ldo = N; d.epi.out_f32 = out_f32 != 0;
+  const bool mfma = precision == 1;
+  const GemmPlan p = plan_gemm(mfma, precision, d, 0, splitk_scratch(mfma), !(d.a_kcontig && d.b_kcontig));
+  *kernel = p.kernel; *tile_m = p.tm; *tile_n = p.tn; *splitk = p.splitk;
   return MSLT_OK;
 }
 
