@@ -259,6 +259,10 @@ int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, void* C, int
 int mslt_debug_plan_gemm(int precision, int M, int N, int K, int a_kcontig, int b_kcontig, int out_f32, int* kernel, int* tile_m,
                          int* tile_n, int* splitk);
 
+/* How a step's forward runs for a batch x seq: the token rows (padded ones included) that go through the layers as one chain of
+ * kernels in rows[0] and those of a second chain beside it in rows[1], 0 where there is none.  Host only. */
+int mslt_debug_plan_chains(const mslt_config* cfg, int batch, int seq, int dropout, int rows[2]);
+
 /* Test aid for the attention of one layer (Section 4.1, the architecture of BERT) through the kernels a step takes for
  * these sizes, forward and, when dctx is not null, backward, on DEVICE operands, enqueued on hip_stream.  precision as
  * in mslt_config: 0 fp32, 1 bf16 (qkv, ctx, dctx, dqkv).  qkv [batch*seq, 3H]: Q | K | V, head h at columns

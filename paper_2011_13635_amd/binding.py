@@ -20,7 +20,7 @@ EXPORTS = [
     "mslt_set_dropout", "mslt_debug_masked",
     "mslt_debug_prefix_output", "mslt_grow", "mslt_sync", "mslt_destroy", "mslt_last_error",
     "mslt_profile_enable", "mslt_profile_read", "mslt_debug_gemm",
-    "mslt_debug_attention", "mslt_debug_plan_gemm",
+    "mslt_debug_attention", "mslt_debug_plan_gemm", "mslt_debug_plan_chains",
 ]
 
 MSLT_OK, MSLT_ERR_ARG, MSLT_ERR_STATE, MSLT_ERR_DATA, MSLT_ERR_HIP, MSLT_ERR_NONFINITE = 0, -1, -2, -3, -4, -5
@@ -93,6 +93,7 @@ def load_library():
     lib.mslt_sync.argtypes = [vp]
     lib.mslt_debug_gemm.argtypes = [vp, vp, vp, vp] + [C.c_int] * 11 + [vp, sz]
     lib.mslt_debug_plan_gemm.argtypes = [C.c_int] * 7 + [P(C.c_int)] * 4
+    lib.mslt_debug_plan_chains.argtypes = [P(Config), C.c_int, C.c_int, C.c_int, P(C.c_int)]
     lib.mslt_debug_attention.argtypes = [vp] + [C.c_int] * 5 + [vp, vp, C.c_float, C.c_float, C.c_uint64] + [vp] * 6
     lib.mslt_destroy.argtypes = [vp]
     lib.mslt_last_error.argtypes = []
@@ -150,6 +151,13 @@ def mslt_debug_plan_gemm(precision, M, N, K, a_kcontig, b_kcontig, out_f32=0):
     out = [C.c_int() for _ in range(4)]
     _check(load_library().mslt_debug_plan_gemm(precision, M, N, K, a_kcontig, b_kcontig, out_f32, *map(C.byref, out)))
     return tuple(x.value for x in out)
+
+
+def mslt_debug_plan_chains(cfg: Config, batch, seq, dropout=False):
+    """Token rows of a step's two forward chains, (rows, 0) for one chain.  Host only."""
+    rows = (C.c_int * 2)()
+    _check(load_library().mslt_debug_plan_chains(C.byref(cfg), batch, seq, int(dropout), rows))
+    return rows[0], rows[1]
 
 
 def mslt_debug_attention(qkv, attn_mask, n_heads, head_width, mask_bias=-10000.0, dropout=0.0, seed=0, dctx=None, stream=None):

@@ -202,6 +202,7 @@ bool gemm_few_supported(const GemmDesc& d);
 // Tile it should take a product with, 0: another kernel should.  rows: d.M, or the rows of the part of a product that
 // has to be computed as that part alone would be (its order of additions is not the other kernels').
 int gemm_few_tile(const GemmDesc& d, int rows);
+int gemm_few_edge(int rows, int N, int K);     // the same by sizes alone
 hipError_t gemm_few(const GemmDesc& d, int tile, hipStream_t s);
 
 // ---- attention ------------------------------------------------------------------------------

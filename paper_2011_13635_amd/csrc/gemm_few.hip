@@ -212,13 +212,13 @@ bool gemm_few_supported(const GemmDesc& d) { return d.a_kcontig && gemm_rows_sup
 // Two 64-wide workgroups on a compute unit with one group in flight beat one with two in flight: 512x3072x768 9.0
 // against 13.7.  A long contraction is better split over workgroups: at 512x768x30592 the 64-wide form took 154, a
 // split by 8 of the 128-wide kernel 53.
-int gemm_few_tile(const GemmDesc& d, int rows) {
-  if (!gemm_few_supported(d)) return 0;
-  const long long tiles = (long long)((rows + 63) / 64) * (d.N / 64);
-  if (4 * tiles <= 256 && d.K <= 8192) return 32;
-  if (tiles <= 512 && d.K <= 4096) return 64;
+int gemm_few_edge(int rows, int N, int K) {
+  const long long tiles = (long long)((rows + 63) / 64) * (N / 64);
+  if (4 * tiles <= 256 && K <= 8192) return 32;
+  if (tiles <= 512 && K <= 4096) return 64;
   return 0;
 }
+int gemm_few_tile(const GemmDesc& d, int rows) { return gemm_few_supported(d) ? gemm_few_edge(rows, d.N, d.K) : 0; }
 
 hipError_t gemm_few(const GemmDesc& d, int tile, hipStream_t s) {
   if (!gemm_few_supported(d) || (tile != 32 && tile != 64)) return hipErrorInvalidValue;

@@ -162,7 +162,7 @@ struct mslt_model {
   // pinned host scalars
   int32_t* h_counters; float* h_loss;
   // last step
-  int few_rows = 0;        // while the forward of a step that belongs on two chains is queued: rows of its first part (see `halves`)
+  int few_rows = 0;        // while the forward of a step that belongs on two chains is queued: rows of its larger part (see plan_chains)
   bool have_grads;
   int last_f, last_k, last_emb, last_B, last_S, last_M;
   const void* last_prefix;
@@ -1166,6 +1166,39 @@ static int layer_backward_top(mslt_model* m, int l, const mslt_batch* bt, int T,
 
 // ---- the stage step -------------------------------------------------------------------------
 // Queues one whole stage step (everything but the final wait) on the model's streams.
+// How many token rows the forward of a step queues on each of two streams; one chain: everything in rows[0], false.
+// The two halves of the batch go through the encoder as two independent chains of kernels, one per
+// stream: where a kernel of one chain leaves compute units idle (a last, partly filled round of
+// workgroups, its ramp-up and its drain) kernels of the other chain take them; four chains on four
+// streams were slower.  The halves meet at a sequence, at any row: the products of the first one leave the rows of the
+// second alone, which takes the padded rows along.  Dropout indexes its decisions by position in the whole batch: the second
+// half's kernels get keys that carry its offset, which has to be a multiple of 4.
+// One chain where the widest product, a feed-forward one, has at most 2^30 operations: such a product lasts about as
+// long as its launch, and a second chain only doubles the launches the host has to queue.  Two chains / one, us:
+//   at the line and below (at most 2^30): 128-wide 2+1 layers 4x64 358 / 289, 32x64 368 / 331, 64x128 421 / 424; 256-wide
+//   4+2 2x128 573 / 519, 16x128 650 / 629; 512-wide 4+2 4x128 650 / 625;
+//   above it: Base 9+3 2x128 (1.1 * 2^30) 1152 / 1170, 4x128 1274 / 1325, 8x128 1504 / 1611, 16x128 1866 / 1886, 64x128
+//   3723 / 4228; Large 18+6 2x128 2554 / 2607, 8x128 3584 / 3763, 32x128 7359 / 7378; 256-wide 32x128 774 / 791;
+//   halves of unequal rows: Base 9+3 3x128 1268 / 1336, 9x128 1582 / 1610, 23x128 2247 / 2436; Large 18+6 3x128 3001 / 3184,
+//   5x128 3414 / 3564, 13x200 6255 / 6554.
+// 512-wide models from 1.5 to 8 times the line are the exception (one chain ahead by up to 4 %: 7x128 750 / 726, 12x100 832 /
+// 809, but 3x512 920 / 945): no line by operations parts them from Base at 2x128.
+// Halves of unequal rows go as one chain also where the larger one has too many rows for the 32-wide few-tile kernel on
+// hidden-wide products while one chain would not leave the few-tile kernel: the chains then last as long as the one, and
+// share the chip.  Base 6+3 3x180 1372 / 1285, 5x112 1299 / 1223, 3x200 1376 / 1305, 5x128 1246 / 1211, 13x40 1229 / 1193; Large
+// 6+3 3x140 1662 / 1571, 10x40 1549 / 1480; on either side 15x40 1189 / 1196 (320 rows each), 5x100 1189 / 1209, Large 3x128
+// 1415 / 1467 and 13x40 1598 / 1605.
+static bool plan_chains(const mslt_model* m, int B, int S, bool dropout, int (&rows)[2]) {
+  const int T = B * S, Tr = m->mfma ? (int)rup(T, 128) : T, R1 = (B + 1) / 2 * S, R2 = Tr - R1;
+  rows[0] = Tr; rows[1] = 0;
+  if (m->dtype != 1 || !m->mfma || B < 2 || (dropout && (long long)R1 * m->nh * S % 4)) return false;
+  if ((double)T * m->F * m->H <= (double)(1 << 29)) return false;
+  if (R1 != R2 && gemm_few_edge(std::max(R1, R2), m->H, m->H) != 32 && gemm_few_edge(Tr, m->F, m->H) && gemm_few_edge(Tr, m->H, m->F))
+    return false;
+  rows[0] = R1; rows[1] = R2;
+  return true;
+}
+
 static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const mslt_batch* bt) {
   if (!m || !bt) return fail(MSLT_ERR_ARG, "null argument");
   if (k < 1 || f < 0 || f + k > m->L)
@@ -1214,29 +1247,14 @@ static int stage_step_enqueue(mslt_model* m, int f, int k, int train_emb, const 
                          Wf(m, T_ELN_G), Wf(m, T_ELN_B), m->cfg.ln_eps, m->x0, e0, T, H, m->V, m->cfg.type_vocab,
                          dspec(m, 0, SITE_EMBEDDING), s));
   }
-  // The two halves of the batch go through the encoder as two independent chains of kernels, one per
-  // stream: where a kernel of one chain leaves compute units idle (a last, partly filled round of
-  // workgroups, its ramp-up and its drain) kernels of the other chain take them; four chains on four
-  // streams were slower.  The halves meet at a sequence, at any row: the products of the first one leave the rows of the
-  // second alone.  Dropout indexes its decisions by position in the whole batch: the second half's kernels get keys that
-  // carry its offset, which has to be a multiple of 4.  Off while event profiling
-  // (queued as one chain then, with the kernels the halves would take, so that the results are the same bits).
-  // One chain where the widest product, a feed-forward one, has at most 2^30 operations: such a product lasts about as
-  // long as its launch, and a second chain only doubles the launches the host has to queue.  Two chains / one, us:
-  //   at the line and below (at most 2^30): 128-wide 2+1 layers 4x64 358 / 289, 32x64 368 / 331, 64x128 421 / 424; 256-wide
-  //   4+2 2x128 573 / 519, 16x128 650 / 629; 512-wide 4+2 4x128 650 / 625;
-  //   above it: Base 9+3 2x128 (1.1 * 2^30) 1152 / 1170, 4x128 1274 / 1325, 8x128 1504 / 1611, 16x128 1866 / 1886, 64x128
-  //   3723 / 4228; Large 18+6 2x128 2554 / 2607, 8x128 3584 / 3763, 32x128 7359 / 7378; 256-wide 32x128 774 / 791.
-  //   unequal halves: Base 9+3 3x128 1258 / 1346, 5x128 1416 / 1402, 11x128 1674 / 1776, 33x100 2517 / 2764, 27x203 with dropout
-  //   3469 / 3930; Large 18+6 3x128 3000 / 3245, 13x200 with dropout 6530 / 7170, 45x200 12510 / 14830 (one chain: the kernels before).
-  // 512-wide models from 1.5 to 8 times the line are the exception (one chain ahead by up to 4 %, 8x128 771 / 742): no
-  // line by operations parts them from Base at 2x128.
-  const int B1 = (B + 1) / 2, R1 = B1 * S;
-  const bool two_chains = m->dtype == 1 && m->mfma && B >= 2 && (!m->drop_thr || (long long)R1 * m->nh * S % 4 == 0) &&
-                          (double)T * m->F * H > (double)(1 << 29);
+  // (see plan_chains; off while event profiling: queued as one chain then, with the kernels the halves would take, so that the
+  // results are the same bits)
+  int rows[2];
+  const bool two_chains = plan_chains(m, B, S, m->drop_thr != 0, rows);
   const bool halves = two_chains && !m->prof.on;
-  m->few_rows = two_chains ? R1 : 0;
-  const FwdPart parts[2] = {{0, B1, R1, s}, {B1, B - B1, Tr - R1, m->side}};
+  const int B1 = rows[0] / S;
+  m->few_rows = two_chains ? std::max(rows[0], rows[1]) : 0;
+  const FwdPart parts[2] = {{0, B1, rows[0], s}, {B1, B - B1, rows[1], m->side}};
   if (halves) {
     HIP_TRY(hipEventRecord(m->ev_fork, s));
     HIP_TRY(hipStreamWaitEvent(m->side, m->ev_fork, 0));
@@ -1619,6 +1637,19 @@ extern "C" int mslt_debug_plan_gemm(int precision, int M, int N, int K, int a_kc
   const bool mfma = precision == 1;
   const GemmPlan p = plan_gemm(mfma, precision, d, 0, splitk_scratch(mfma), !(d.a_kcontig && d.b_kcontig));
   *kernel = p.kernel; *tile_m = p.tm; *tile_n = p.tn; *splitk = p.splitk;
+  return MSLT_OK;
+}
+
+extern "C" int mslt_debug_plan_chains(const mslt_config* cfg, int batch, int seq, int dropout, int rows[2]) {
+  int rc = check_config(cfg);
+  if (rc) return rc;
+  if (!rows || batch < 1 || seq < 1 || batch > cfg->max_batch || seq > cfg->max_seq)
+    return fail(MSLT_ERR_ARG, "debug_plan_chains: null output, or a batch outside the configuration");
+  mslt_model m{};
+  setup_dims(&m, cfg);
+  int r[2];
+  plan_chains(&m, batch, seq, dropout != 0, r);
+  rows[0] = r[0]; rows[1] = r[1];
   return MSLT_OK;
 }
 
