@@ -809,9 +809,11 @@ bool gemm_phase_supported(const GemmDesc& d, int tile_m, int tile_n) {
   if (d.epi.accumulate && !d.epi.out_f32) return false;
   auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
   if (!al(d.A) || !al(d.B) || !al(d.epi.out) || !al(d.epi.out2) || !al(d.epi.aux) || !al(d.epi.bias)) return false;
-  // byte offsets of a tile inside its operands' views stay below 2^31
-  const long long a_span = d.a_kcontig ? (long long)tile_m * d.lda + d.K : (long long)d.K * d.lda + tile_m;
-  const long long b_span = d.b_kcontig ? (long long)tile_n * d.ldb + d.K : (long long)d.K * d.ldb + tile_n;
+  // byte offsets of a tile inside its operands' views stay below 2^31, those of the loads queued past the last k tile (up to
+  // three more) among them
+  const long long k_end = d.K + 4 * 64;
+  const long long a_span = d.a_kcontig ? (long long)tile_m * d.lda + k_end : k_end * d.lda + tile_m;
+  const long long b_span = d.b_kcontig ? (long long)tile_n * d.ldb + k_end : k_end * d.ldb + tile_n;
   return 2 * a_span < 0x7fffffffLL && 2 * b_span < 0x7fffffffLL;
 }
 hipError_t gemm_phase(const GemmDesc& d, int tile_m, int tile_n, int splitk, float* partials, hipStream_t s, bool keep_partials) {

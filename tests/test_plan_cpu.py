@@ -49,3 +49,15 @@ def test_forward_chains_with_dropout_meet_where_its_quads_do():
     sh.update(n_heads=6)
     cfg = binding.make_config(synth.ModelShape(**sh), 64, 512, 1)
     assert binding.mslt_debug_plan_chains(cfg, 25, 203, True) == (5120, 0) != binding.mslt_debug_plan_chains(cfg, 25, 203)
+
+
+@pytest.mark.parametrize("N,tile", [(16384, (256, 256)), (16256, (256, 128))])
+def test_offsets_of_loads_past_the_last_k_tile_count(N, tile):
+    # the turn-taking tiles queue up to three k tiles past the end: the byte offset of a k-strided operand's row K + 190 has to
+    # fit 31 bits, where those of the operand itself do
+    limit = 2**31
+    fits = (limit // (2 * N) - 256 - 1) // 64 * 64
+    beyond = (limit // (2 * N) - 1) // 64 * 64
+    assert 2 * N * (fits + 256) < limit and 2 * N * beyond < limit < 2 * N * (beyond + 190)
+    assert binding.mslt_debug_plan_gemm(1, 4096, N, fits, 1, 0)[:3] == (5,) + tile
+    assert binding.mslt_debug_plan_gemm(1, 4096, N, beyond, 1, 0)[:3] != (5,) + tile
