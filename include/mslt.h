@@ -246,12 +246,30 @@ int mslt_profile_read(mslt_model* m, mslt_profile_entry* out, int cap, int* n);
  * few-tile kernel, a_kcontig != 0, sizes as kernel 1, tile_m = tile_n = 32 or 64.  kernel 5: the tiles a step uses where
  * the rows of C are no multiple of the tile, a_kcontig != 0, any M, N % tile_n == 0 (128 at least), K % 64 == 0: 256x256,
  * 256x384, 256x128, 128x256, 128x192, 64x64 or 32x32.  kernel 6: fp32 kernel of the step, fp32 operands, out_f32 != 0,
- * rows of a multiple of 16 bytes.  splitk > 1 (not kernels 3 and 5) splits the contraction over
+ * rows of a multiple of 16 bytes.  kernel 7: a grouped launch of weight gradients, of this one product: both operands
+ * k-strided, out_f32 != 0, 256x256, 256x128 or 128x128.  splitk > 1 (not kernels 3, 5 and 7) splits the contraction over
  * workgroups and needs `partials`, DEVICE scratch of at least splitk*M*N*4 bytes (partial_bytes says how large it is).  Returns MSLT_ERR_ARG for a shape or
  * choice the kernel does not take; nothing is enqueued then.  Does not block. */
 int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, void* C, int M, int N, int K, int a_kcontig,
                     int b_kcontig, int out_f32, int kernel, int tile_m, int tile_n, int tile_k, int splitk,
                     void* partials, size_t partial_bytes);
+
+/* The same with what a step lets a product end in: bias, then dropout, then GELU, a multiplication by a stored GELU
+ * derivative or an addition, then (out_f32 only) addition to what C holds.  All pointers DEVICE, 16-byte aligned. */
+typedef struct {
+  const float* bias;     /* [N], or null */
+  int act;               /* 0 none, 1 GELU, 2 multiply by aux, 3 add aux */
+  void* gelu_grad;       /* act 1: [M,N], receives GELU' of the value before, or null.  bf16 kernels: 16-bit code
+                            round((x + 1/4) * 32768); fp32 kernels: fp32 */
+  const void* aux;       /* act 2: [M,N] as gelu_grad; act 3: [M,N] of the operands' type, or fp32 when aux_f32 != 0 */
+  int aux_f32;
+  float dropout;         /* > 0: keep decisions of mslt_set_dropout for (seed, step 0, layer 0, site 2) */
+  uint64_t seed;
+  int accumulate;
+} mslt_debug_epilogue;
+int mslt_debug_gemm_epilogue(void* hip_stream, const void* A, const void* B, void* C, int M, int N, int K, int a_kcontig,
+                             int b_kcontig, int out_f32, int kernel, int tile_m, int tile_n, int tile_k, int splitk,
+                             void* partials, size_t partial_bytes, const mslt_debug_epilogue* epilogue);
 
 /* Which of those kernels a step takes for a product of these sizes, and how: *kernel as above, its tile (0 where the kernel
  * chooses) and the number of parts of the contraction (for weight gradients before the scratch at hand is looked at).

@@ -20,7 +20,7 @@ EXPORTS = [
     "mslt_set_dropout", "mslt_debug_masked",
     "mslt_debug_prefix_output", "mslt_grow", "mslt_sync", "mslt_destroy", "mslt_last_error",
     "mslt_profile_enable", "mslt_profile_read", "mslt_debug_gemm",
-    "mslt_debug_attention", "mslt_debug_plan_gemm", "mslt_debug_plan_chains",
+    "mslt_debug_attention", "mslt_debug_plan_gemm", "mslt_debug_plan_chains", "mslt_debug_gemm_epilogue",
 ]
 
 MSLT_OK, MSLT_ERR_ARG, MSLT_ERR_STATE, MSLT_ERR_DATA, MSLT_ERR_HIP, MSLT_ERR_NONFINITE = 0, -1, -2, -3, -4, -5
@@ -53,6 +53,11 @@ class Opt(C.Structure):
 class TensorDesc(C.Structure):
     _fields_ = [("name", C.c_char * 32), ("layer", C.c_int), ("rows", C.c_int), ("cols", C.c_int),
                 ("decays", C.c_int), ("offset", C.c_size_t), ("count", C.c_size_t)]
+
+
+class DebugEpilogue(C.Structure):
+    _fields_ = [("bias", C.c_void_p), ("act", C.c_int), ("gelu_grad", C.c_void_p), ("aux", C.c_void_p), ("aux_f32", C.c_int),
+                ("dropout", C.c_float), ("seed", C.c_uint64), ("accumulate", C.c_int)]
 
 
 class ProfileEntry(C.Structure):
@@ -92,6 +97,7 @@ def load_library():
     lib.mslt_profile_read.argtypes = [vp, P(ProfileEntry), C.c_int, P(C.c_int)]
     lib.mslt_sync.argtypes = [vp]
     lib.mslt_debug_gemm.argtypes = [vp, vp, vp, vp] + [C.c_int] * 11 + [vp, sz]
+    lib.mslt_debug_gemm_epilogue.argtypes = lib.mslt_debug_gemm.argtypes + [P(DebugEpilogue)]
     lib.mslt_debug_plan_gemm.argtypes = [C.c_int] * 7 + [P(C.c_int)] * 4
     lib.mslt_debug_plan_chains.argtypes = [P(Config), C.c_int, C.c_int, C.c_int, P(C.c_int)]
     lib.mslt_debug_attention.argtypes = [vp] + [C.c_int] * 5 + [vp, vp, C.c_float, C.c_float, C.c_uint64] + [vp] * 6
@@ -133,17 +139,22 @@ def lamb(lr=0.00088, beta1=0.9, beta2=0.999, eps=1e-6, weight_decay=0.01, bias_c
 
 
 def mslt_debug_gemm(a, b, c, M, N, K, a_kcontig, b_kcontig, kernel, tile_m=0, tile_n=0, tile_k=64, splitk=1,
-                    partials=None, stream=None):
-    """One product through a chosen kernel.  a, b: torch bf16 device tensors (fp32 for kernel 4); c: bf16 or fp32 device tensor
-    [M, N]; partials: uint8/fp32 device tensor for split-k.  Enqueues only."""
+                    partials=None, stream=None, epilogue=None):
+    """One product through a chosen kernel.  a, b: torch bf16 device tensors (fp32 for kernels 4 and 6); c: bf16 or fp32 device
+    tensor [M, N]; partials: uint8/fp32 device tensor for split-k; epilogue: dict of the fields of mslt_debug_epilogue, device
+    tensors for its pointers.  Enqueues only."""
     import torch
     out_f32 = int(c.dtype == torch.float32)
     st = stream if stream is not None else torch.cuda.current_stream(a.device)
     pb = partials.numel() * partials.element_size() if partials is not None else 0
-    _check(load_library().mslt_debug_gemm(C.c_void_p(st.cuda_stream), C.c_void_p(a.data_ptr()), C.c_void_p(b.data_ptr()),
-                                          C.c_void_p(c.data_ptr()), M, N, K, int(a_kcontig), int(b_kcontig), out_f32, kernel,
-                                          tile_m, tile_n, tile_k, splitk,
-                                          C.c_void_p(partials.data_ptr()) if partials is not None else None, pb))
+    args = (C.c_void_p(st.cuda_stream), C.c_void_p(a.data_ptr()), C.c_void_p(b.data_ptr()), C.c_void_p(c.data_ptr()), M, N, K,
+            int(a_kcontig), int(b_kcontig), out_f32, kernel, tile_m, tile_n, tile_k, splitk,
+            C.c_void_p(partials.data_ptr()) if partials is not None else None, pb)
+    if epilogue is None:
+        _check(load_library().mslt_debug_gemm(*args))
+    else:
+        e = DebugEpilogue(**{k: v.data_ptr() if isinstance(v, torch.Tensor) else v for k, v in epilogue.items()})
+        _check(load_library().mslt_debug_gemm_epilogue(*args, C.byref(e)))
 
 
 def mslt_debug_plan_gemm(precision, M, N, K, a_kcontig, b_kcontig, out_f32=0):

@@ -1574,6 +1574,12 @@ extern "C" int mslt_grow(mslt_model* m, int n_present, int n_new) {
 extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, void* C, int M, int N, int K, int a_kcontig,
                                int b_kcontig, int out_f32, int kernel, int tile_m, int tile_n, int tile_k, int splitk,
                                void* partials, size_t partial_bytes) {
+  return mslt_debug_gemm_epilogue(hip_stream, A, B, C, M, N, K, a_kcontig, b_kcontig, out_f32, kernel, tile_m, tile_n, tile_k,
+                                  splitk, partials, partial_bytes, nullptr);
+}
+extern "C" int mslt_debug_gemm_epilogue(void* hip_stream, const void* A, const void* B, void* C, int M, int N, int K,
+                                        int a_kcontig, int b_kcontig, int out_f32, int kernel, int tile_m, int tile_n, int tile_k,
+                                        int splitk, void* partials, size_t partial_bytes, const mslt_debug_epilogue* e) {
   if (!A || !B || !C) return fail(MSLT_ERR_ARG, "debug_gemm: null operand");
   if (M < 1 || N < 1 || K < 1) return fail(MSLT_ERR_ARG, "debug_gemm: non-positive size");
   if (splitk < 1) return fail(MSLT_ERR_ARG, "debug_gemm: splitk must be at least 1");
@@ -1585,6 +1591,19 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
   d.a_kcontig = a_kcontig != 0; d.b_kcontig = b_kcontig != 0;
   d.lda = d.a_kcontig ? K : M; d.ldb = d.b_kcontig ? K : N;
   d.epi.out = C; d.epi.ldo = N; d.epi.out_f32 = out_f32 != 0;
+  if (e) {
+    if (e->act < EPI_NONE || e->act > EPI_ADD || ((e->act == EPI_MUL || e->act == EPI_ADD) != (e->aux != nullptr)) ||
+        (e->gelu_grad && e->act != EPI_GELU) || (e->aux_f32 && e->act != EPI_ADD) || (e->accumulate && !out_f32) ||
+        !(e->dropout >= 0.f && e->dropout < 1.f) || (e->dropout > 0.f && N % 4))
+      return fail(MSLT_ERR_ARG, "debug_gemm: the parts of the epilogue do not belong together");
+    d.epi.bias = e->bias; d.epi.act = e->act; d.epi.out2 = e->gelu_grad; d.epi.aux = e->aux; d.epi.ldaux = N;
+    d.epi.aux_f32 = e->aux_f32 != 0; d.epi.accumulate = e->accumulate != 0; d.epi.drop_ld = N;
+    if (e->dropout > 0.f) {
+      d.epi.drop.key = drop_key(e->seed, 0, 0, SITE_ATTN_OUT);
+      d.epi.drop.thr = (uint32_t)lrintf(e->dropout * 65536.0f);
+      d.epi.drop.scale = 1.0f / (1.0f - e->dropout);
+    }
+  }
   if (kernel == 0 || kernel == 4) {
     const int dtype = kernel == 0, slab = dtype ? 64 : 32;
     if (splitk > (K + slab - 1) / slab || (!dtype && !out_f32))
@@ -1619,8 +1638,14 @@ extern "C" int mslt_debug_gemm(void* hip_stream, const void* A, const void* B, v
     if (!out_f32 || !gemm_f32_supported(d) || splitk > (K + 31) / 32)
       return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d, splitk %d not taken by the fp32 kernel", M, N, K, splitk);
     HIP_TRY(gemm_f32(d, splitk, (float*)partials, st));
+  } else if (kernel == 7) {
+    bool ok = false;
+    for (auto& t : kGroupTile) ok = ok || (tile_m == t[0] && tile_n == t[1]);
+    if (!ok || d.a_kcontig || d.b_kcontig || !out_f32 || splitk != 1 || tile_k != 64 || !gemm_ring_supported(d, tile_m, tile_n, 64))
+      return fail(MSLT_ERR_ARG, "debug_gemm: shape %dx%dx%d not taken by a grouped launch with tile %dx%d", M, N, K, tile_m, tile_n);
+    HIP_TRY(gemm_ring_grouped_tn(&d, 1, tile_m, tile_n, st));
   } else {
-    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 6");
+    return fail(MSLT_ERR_ARG, "debug_gemm: kernel must be 0 to 7");
   }
   return MSLT_OK;
 }

@@ -97,7 +97,8 @@ def test_ctypes_structs_match_the_header_layout(tmp_path, repo_root):
     if shutil.which("gcc") is None:
         pytest.skip("no C compiler")
     structs = {"mslt_config": binding.Config, "mslt_batch": binding.Batch, "mslt_opt": binding.Opt,
-               "mslt_tensor_desc": binding.TensorDesc, "mslt_profile_entry": binding.ProfileEntry}
+               "mslt_tensor_desc": binding.TensorDesc, "mslt_profile_entry": binding.ProfileEntry,
+               "mslt_debug_epilogue": binding.DebugEpilogue}
     lines = ['#include <stdio.h>', '#include <stddef.h>', '#include "mslt.h"', 'int main(void) {']
     for cname, cls in structs.items():
         lines.append(f'  printf("{cname} size %zu\\n", sizeof({cname}));')

@@ -32,6 +32,15 @@ def test_grouped_three_per_group_with_dropout_bf16_base_width():
     r["model"].close()
 
 
+def test_grouped_bf16_large_width():
+    # BERT-Large width: a layer's weight gradients are 192 tiles of 256x256, which one launch computes; the lower layer's
+    # adds to what the upper one's wrote
+    sh = synth.ModelShape(n_layers=2, hidden=1024, n_heads=16, ffn=4096, vocab=1024, layers_per_group=2)
+    r = run_case(sh, 3, 100, 0, 2, True, 1, ragged=True, seed=13, std=0.02, perturb=0.05, dropout=(0.1, 3, 4))
+    print("grouped large", assert_parity(r, 1, "grouped large 0/2"))
+    r["model"].close()
+
+
 def test_grouped_schedule_update_and_growth():
     # stage 1 trains group 0 (+ embeddings), growth copies it into group 1, stage 2 trains group 1 only
     sh = grouped_tiny()
