@@ -1,5 +1,6 @@
-"""Tiles of a matrix product whose rows are no multiple of the tile: the right result in every row, none past the end
-written, none past the end of A read (its buffer ends there); and a step whose two forward chains meet inside a tile."""
+"""Tiles of a matrix product whose rows are no multiple of the tile: the right result in every row and none past the end
+written; and a step whose two forward chains meet inside a tile.  (Whether rows past the end of A are read shows in no
+result: they would feed rows that are not written.)"""
 import numpy as np
 import pytest
 
