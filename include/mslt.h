@@ -242,7 +242,7 @@ int mslt_profile_read(mslt_model* m, mslt_profile_entry* out, int cap, int* n);
  * kernel 0: guarded kernel (any shape); kernel 4: the same on fp32 operands, out_f32 != 0.  kernel 1: 128-wide MFMA kernel, tile_m 0 (chosen by
  * shape), 128 or 256; M % 128 == 0, N % 128 == 0, K % 64 == 0.  kernel 2: large-tile kernel fed by
  * direct global-to-LDS loads, tile_m x tile_n one of 256x256, 256x128, 128x256, 128x128, ring stage
- * tile_k 64 (or 32, not for 128x128); M % tile_m == 0, N % tile_n == 0, K % tile_k == 0.  kernel 3:
+ * tile_k 64 (or 32, not for 128x128; 256x256 with tile_k 64 runs the turn-taking kernel that a step takes); M % tile_m == 0, N % tile_n == 0, K % tile_k == 0.  kernel 3:
  * few-tile kernel, a_kcontig != 0, sizes as kernel 1, tile_m = tile_n = 32 or 64.  kernel 5: the tiles a step uses where
  * the rows of C are no multiple of the tile, a_kcontig != 0, any M, N % tile_n == 0 (128 at least), K % 64 == 0: 256x256,
  * 256x384, 256x128, 128x256, 128x192, 64x64 or 32x32.  kernel 6: fp32 kernel of the step, fp32 operands, out_f32 != 0,

@@ -189,10 +189,10 @@ hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int spli
 
 // Large tiles whose wavefronts take turns (bf16): 256x256 in any operand layout; 256x384, 256x128 and 128x192 with a
 // k-contiguous A.  Any M when A is k-contiguous (rows past the end are neither read nor written), N % tile_n == 0,
-// K % 64 == 0.  Only 256x256 and 256x128 split the contraction; keep_partials as in gemm_ring.
+// K % 64 == 0.  Only 256x256 splits the contraction, and only where both operands are k-strided does a product
+// accumulate or drop elements of another result than a plain bf16 one.
 bool gemm_phase_supported(const GemmDesc& d, int tile_m, int tile_n);
-hipError_t gemm_phase(const GemmDesc& d, int tile_m, int tile_n, int splitk, float* partials, hipStream_t s,
-                      bool keep_partials = false);
+hipError_t gemm_phase(const GemmDesc& d, int tile_m, int tile_n, int splitk, float* partials, hipStream_t s);
 // as gemm_ring_grouped_tn, with tiles of 256x256
 hipError_t gemm_phase_grouped_tn(const GemmDesc* d, int n, hipStream_t s);
 

@@ -8,11 +8,11 @@
 // A workgroup of eight wavefronts owns a TM x TN tile (256x256: 2x4 wavefronts of 128x64;
 // 256x128 and 128x256: 64x64 per wavefront).  Both operands travel global memory -> LDS
 // directly (buffer loads with the LDS bit, 16 bytes per lane, no register staging) through a
-// ring of NS stages of 32 k each, NS-1 tiles ahead of the matrix cores; one workgroup barrier
-// per 32 k.  An operand whose k index is contiguous in memory sits in LDS as [rows][32 k] with
-// the four 16-byte chunks of a row XOR-swizzled by the row index, and its MFMA fragments are
+// ring of NS stages of RK k each (64 in a step), NS-1 tiles ahead of the matrix cores; one workgroup barrier
+// per stage.  An operand whose k index is contiguous in memory sits in LDS as [rows][RK k] with
+// the 16-byte chunks of a row XOR-swizzled by the row index, and its MFMA fragments are
 // plain 16-byte reads.  An operand whose k index is the strided one (the weight in dX = dY.W,
-// both operands in dW = dY^T.X) is copied as it lies, [32 k][rows], with the 16-byte chunks of a
+// both operands in dW = dY^T.X) is copied as it lies, [RK k][rows], with the 16-byte chunks of a
 // k row XOR-swizzled by k, and its fragments come from the transposing LDS read
 // (ds_read_b64_tr_b16: sixteen lanes that each fetch four consecutive rows of one k receive four
 // consecutive k of one row), so no operand is ever transposed in registers or in HBM.
@@ -388,7 +388,8 @@ constexpr int ring_depth(int TM, int TN, int RK) {
   int n = 160 * 1024 / ((TM + TN) * RK * 2);
   return n > 6 ? 6 : n;
 }
-// every tile shape in every operand layout
+// Every tile shape in every operand layout.  A step launches 128x256 with a k-contiguous A, 128x128 and the grouped ones; the
+// others, those with stages of 32 k among them, serve the measurements and tests that pick a tile themselves.
 #define MSLT_RING_INSTANCES(TM, TN, RK)                                                      \
   template __global__ void k_gemm_ring<TM, TN, RK, ring_depth(TM, TN, RK), true, true>(Params);   \
   template __global__ void k_gemm_ring<TM, TN, RK, ring_depth(TM, TN, RK), true, false>(Params);  \
@@ -491,13 +492,13 @@ bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk, bool
   const long long a_span = d.a_kcontig ? (long long)tile_m * d.lda + d.K : (long long)d.K * d.lda + tile_m;
   const long long b_span = d.b_kcontig ? (long long)tile_n * d.ldb + d.K : (long long)d.K * d.ldb + tile_n;
   if (2 * a_span >= 0x7fffffffLL || 2 * b_span >= 0x7fffffffLL) return false;
-  return true;
+  return tile_m != 256 || tile_n != 256 || rk != 64 || gemm_phase_supported(d, 256, 256);      // (gemm_ring hands these on)
 }
 
 hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int splitk, float* partials, hipStream_t s,
                      bool keep_partials) {
   if (!gemm_ring_supported(d, tile_m, tile_n, rk, splitk == 1)) return hipErrorInvalidValue;
-  if (tile_m == 256 && tile_n == 256 && rk == 64) return gemm_phase(d, 256, 256, splitk, partials, s, keep_partials);
+  if (tile_m == 256 && tile_n == 256 && rk == 64) return keep_partials ? hipErrorInvalidValue : gemm_phase(d, 256, 256, splitk, partials, s);
   if (keep_partials && (!d.epi.out_f32 || d.epi.bias || d.epi.act != EPI_NONE || d.epi.drop.thr || d.epi.out2))
     return hipErrorInvalidValue;
   if (splitk < 1 || splitk > d.K / rk) return hipErrorInvalidValue;
