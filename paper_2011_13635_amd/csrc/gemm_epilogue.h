@@ -37,19 +37,6 @@ static __device__ __forceinline__ bool epilogue_reads_aux(const Epilogue& e) {
 static __device__ __forceinline__ uint4 load_aux8(const Epilogue& e, int m, int n) {
   return *reinterpret_cast<const uint4*>(reinterpret_cast<const bf16*>(e.aux) + (size_t)m * e.ldaux + n);
 }
-// The bias of a bf16 result is what the accumulators of the large and the 128-wide tiles start from; that of an fp32 result
-// (the logits) is added to the sum, so that the sum rounds at its own magnitude (bias in front, as large as the sum: error
-// of the result 2.1e-7 instead of 1.0e-7 at 768 products; rounded to bf16 there is no difference, 1.66e-3 either way).
-static __device__ __forceinline__ const float* early_bias(const Epilogue& e) { return e.out_f32 ? nullptr : e.bias; }
-static __device__ __forceinline__ void late_bias(const Epilogue& e, int n, float (&bias)[8]) {
-  float4 b0 = make_float4(0.f, 0.f, 0.f, 0.f), b1 = b0;
-  if (e.out_f32 && e.bias) {
-    b0 = *reinterpret_cast<const float4*>(e.bias + n);
-    b1 = *reinterpret_cast<const float4*>(e.bias + n + 4);
-  }
-  bias[0] = b0.x; bias[1] = b0.y; bias[2] = b0.z; bias[3] = b0.w;
-  bias[4] = b1.x; bias[5] = b1.y; bias[6] = b1.z; bias[7] = b1.w;
-}
 // raw: the 8 per-element operand values of this position (only read when the epilogue uses them);
 // callers load it well ahead so its latency is not paid here
 // EXTRAS: the rarely used parts (dropout of the result, accumulation into the output) are compiled

@@ -202,13 +202,11 @@ __global__ void __launch_bounds__(2 * BM) k_gemm_mfma(MfmaParams p) {
   const int kbeg = kt_lo * BK;
   const int nk = (int)((long long)(split + 1) * nkt / p.splitk) - kt_lo;
 
-  // the accumulators start from the bias of the lane's column (unless the result is fp32), as in the large tiles (the same
-  // bits whichever is taken)
+  // the accumulators start from the bias of the lane's column, as in the large tiles (the same bits whichever is taken)
   f32x16_t acc[2][2];
-  const float* const bias0 = early_bias(p.epi);
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const float b0 = bias0 && p.splitk == 1 ? bias0[n0 + 64 * wn + 32 * j + (lane & 31)] : 0.f;
+    const float b0 = p.epi.bias && p.splitk == 1 ? p.epi.bias[n0 + 64 * wn + 32 * j + (lane & 31)] : 0.f;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -298,6 +296,7 @@ __global__ void __launch_bounds__(2 * BM) k_gemm_mfma(MfmaParams p) {
   const int n = n0 + 64 * wn + cc;
   const int mrow = m0 + 64 * wm + (lane >> 3);      // first of this lane's 8 rows (stride 8)
   Epilogue e = p.epi;
+  const float bias[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // already in the accumulators
   uint4 raw[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) raw[i] = make_uint4(0, 0, 0, 0);
@@ -312,8 +311,6 @@ __global__ void __launch_bounds__(2 * BM) k_gemm_mfma(MfmaParams p) {
       for (int i = 0; i < 8; ++i) raw[i] = load_aux8(e, mrow + 8 * i, n);
     }
   }
-  float bias[8];
-  late_bias(e, n, bias);
 
   // stage this wavefront's 64x64 quarter in LDS (all operand reads are behind the last barrier)
   float* stage = reinterpret_cast<float*>(smem) + wave * 64 * EPI_LD;

@@ -16,7 +16,8 @@
 // Each block of reads ends with its own wait.
 //
 // Products are formed transposed, so that a lane holds four consecutive columns of a row: bias (it is what the
-// accumulators start from, unless the result is fp32: as part of the epilogue its loads took 9 us per tile), GELU and dropout work on registers, and
+// accumulators start from: as part of the epilogue its loads took 9 us per tile; a step's products with a bias have bf16
+// results, whose error is 1.66e-3 either way), GELU and dropout work on registers, and
 // a result goes through LDS in its final type, 16 bytes per lane and whole cache lines per store (stores straight from
 // the registers, 32 bytes per row, took 4 us longer per tile).
 //
@@ -268,13 +269,11 @@ __device__ __forceinline__ void finish_strip(const Epilogue& e, const f32x16_t (
       for (int g = 0; g < 4; ++g)
         *reinterpret_cast<float4*>(st + r32 * LD + 32 * j + 8 * g + 4 * half) =
             make_float4(c[j][4 * g], c[j][4 * g + 1], c[j][4 * g + 2], c[j][4 * g + 3]);
-    float bias[8];
-    if constexpr (64 % CHUNKS == 0) late_bias(e, n + 8 * (lane % CHUNKS), bias);
+    const float bias[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // already in the accumulators
 #pragma unroll
     for (int i = 0; i < 2 * NBLK; ++i) {
       const int x = 64 * i + lane, row = x / CHUNKS, cc = 8 * (x % CHUNKS);
       if (m + row >= m_end) continue;
-      if constexpr (64 % CHUNKS != 0) late_bias(e, n + cc, bias);
       const float4 x0 = *reinterpret_cast<const float4*>(st + row * LD + cc), x1 = *reinterpret_cast<const float4*>(st + row * LD + cc + 4);
       float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
       epilogue8<FIN == FIN_STAGED_EXTRAS>(e, m + row, n + cc, v, bias, raw[i]);
@@ -342,7 +341,7 @@ __device__ __forceinline__ void phase_tile(const Params& p, const int wg) {
   Frags<B_KC, 2> fb; fb.init(lane, 64 * wn, lds_base);
 
   f32x16_t acc[2][2][2];     // [A half][B half][32-column block]
-  const float* const bias = p.splitk > 1 ? nullptr : early_bias(p.epi);
+  const float* const bias = p.splitk > 1 ? nullptr : p.epi.bias;
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -444,8 +443,6 @@ __global__ void __launch_bounds__(512) k_gemm_phase_grouped(GroupParams gp) {
 // accumulator registers; what is left holds the fragments of 32 k of 64 rows of either operand.  A k tile is the slots
 // A0 A1 B0 B1 B2, two k tiles fill the LDS.  It is gone through twice, k 0..31 and 32..63: in a pass the A fragments are
 // read with the first third.  Slots are refilled in the second pass, behind the step that reads them last.
-// (The ends of a strip find ten registers too few and spill them, all behind the k loop; with the bias loaded eight values
-// later there is no spill, and 1280x30720x768 with an fp32 result takes 87 us instead of 82.)
 template <bool KC>
 struct HalfFrags {      // two 32-row blocks, `apart` bytes from each other, x 32 k: f[block][step]
   unsigned off[KC ? 4 : 2];
@@ -494,7 +491,7 @@ __global__ void __launch_bounds__(512) k_gemm_wide(Params p) {
   for (int j = 0; j < 3; ++j)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      start_block(early_bias(p.epi), at.n0 + 128 * j + 64 * wn + 32 * b, lane, acc[0][j][b]);
+      start_block(p.epi.bias, at.n0 + 128 * j + 64 * wn + 32 * b, lane, acc[0][j][b]);
       acc[1][j][b] = acc[0][j][b];
     }
 
@@ -593,7 +590,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_pair(Params p) {
   f32x16_t acc[2][2][2];     // [A half][32-row block][32-column block]
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
-    start_block(early_bias(p.epi), at.n0 + 64 * wn + 32 * x, lane, acc[0][0][x]);
+    start_block(p.epi.bias, at.n0 + 64 * wn + 32 * x, lane, acc[0][0][x]);
     acc[0][1][x] = acc[1][0][x] = acc[1][1][x] = acc[0][0][x];
   }
   auto issue = [&](int kind, int t, unsigned slot) {      // 0: B; 1, 2: A halves
@@ -700,7 +697,7 @@ __global__ void __launch_bounds__(512) k_gemm_slim(Params p) {
   }
   f32x16_t acc[C];
 #pragma unroll
-  for (int x = 0; x < C; ++x) start_block(early_bias(p.epi), at.n0 + 32 * C * wn + 32 * x, lane, acc[x]);
+  for (int x = 0; x < C; ++x) start_block(p.epi.bias, at.n0 + 32 * C * wn + 32 * x, lane, acc[x]);
 
 #pragma unroll
   for (int q = 0; q < BUFS - 1; ++q) issue(q, q * TILE);

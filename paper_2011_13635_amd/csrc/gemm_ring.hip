@@ -221,13 +221,12 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
   FragsA fa; fa.init(lane, WTM * wm);
   FragsB fb; fb.init(lane, WTN * wn);
 
-  // the accumulators start from the bias of the lane's column (unless the result is fp32), as those of gemm_phase.hip do: a
-  // product is the same bits whichever of these tiles it goes to
+  // the accumulators start from the bias of the lane's column, as those of gemm_phase.hip do: a product is the same bits
+  // whichever of these tiles it goes to
   f32x16_t acc[MI][NI];
-  const float* const bias0 = early_bias(p.epi);
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
-    const float b0 = bias0 && p.splitk == 1 ? bias0[n0 + WTN * wn + 32 * j + (lane & 31)] : 0.f;
+    const float b0 = p.epi.bias && p.splitk == 1 ? p.epi.bias[n0 + WTN * wn + 32 * j + (lane & 31)] : 0.f;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -322,8 +321,7 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
     e.out_f32 = 1;
   }
   const int n = n0 + WTN * wn + cc;
-  float bias[8];
-  late_bias(e, n, bias);
+  const float bias[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // already in the accumulators
   float* stage = reinterpret_cast<float*>(smem) + wave * 64 * EPI_LD;
 #pragma unroll
   for (int pass = 0; pass < MI / 2; ++pass) {

@@ -120,25 +120,6 @@ def test_parts_that_do_not_belong_together_are_refused():
         assert ei.value.code == binding.MSLT_ERR_ARG
 
 
-@pytest.mark.parametrize("kernel,tm,tn", TILES)
-@pytest.mark.parametrize("bkc", [1, 0])
-def test_fp32_result_gets_its_bias_after_the_sum(kernel, tm, tn, bkc):
-    # an fp32 result (the logits) is the sum of the products and then one addition: with the bias in front of the sum every
-    # addition would round at the larger magnitude
-    import torch
-    M, n, k = (256 if kernel == 1 else 131), 768, 448
-    g = torch.Generator().manual_seed(8)
-    a = torch.randn(M, k, generator=g).to(torch.bfloat16).cuda()
-    b = torch.randn((n, k) if bkc else (k, n), generator=g).to(torch.bfloat16).cuda()
-    bias = (torch.randn(n, generator=g) * 64.0).cuda()
-    out = []
-    for end in (None, {"bias": bias}):
-        c = torch.full((M, n), float("nan"), device="cuda:0")
-        binding.mslt_debug_gemm(a, b, c, M, n, k, 1, bkc, kernel, tm, tn, 64, 1, None, epilogue=end)
-        out.append(c)
-    assert torch.equal(out[1], out[0] + bias)
-
-
 @pytest.mark.parametrize("kernel,tm,tn", [(1, 128, 0), (2, 256, 256), (2, 128, 256), (2, 128, 128)])
 @pytest.mark.parametrize("bkc", [1, 0])
 def test_split_contraction_gets_its_bias_once(kernel, tm, tn, bkc):
