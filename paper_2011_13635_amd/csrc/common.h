@@ -173,8 +173,8 @@ hipError_t gemm_mfma(const GemmDesc& d, int splitk, float* partials, hipStream_t
                      int force_dma = -1);
 
 // Large-tile MFMA kernel (bf16 only): tile_m x tile_n of 256x256, 256x128, 128x256 or 128x128, both operands loaded
-// global -> LDS directly in any of the three layouts; M % tile_m == 0 (with any_rows and a k-contiguous A any M: rows past
-// the end are neither read nor written), N % tile_n == 0.
+// global -> LDS directly in any of the three layouts; M % tile_m == 0 (128x256 with any_rows, rk 64 and a k-contiguous A: any M,
+// rows past the end are neither read nor written), N % tile_n == 0.
 // rk: k extent of a ring stage, 32 or 64 (K % rk == 0).
 bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk, bool any_rows = false);
 // Up to gemm_ring_group_max() products whose operands are both k-strided (weight gradients) as one launch of

@@ -150,7 +150,10 @@ constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | 0x70 | ((vm >> 
 // One workgroup's tile of one product; wg: the workgroup's index among the product's workgroups (the index
 // of the launch, or of the product's range of a grouped launch, which starts at a multiple of 8 so that
 // wg % 8 is still the XCD the hardware has put the workgroup on).
-template <int TM, int TN, int RK, int NS, bool A_KC, bool B_KC>
+// RAG: M is no multiple of TM (A k-contiguous, not split).  Whole tiles carry no guards: they kept the loads and stores of a
+// strip apart.  128x256 tiles, us, with guards and a bias awaited in front of the operands / now: 8192x2304x768 43.9 / 42.9,
+// 8192x3072x768 50.3 / 49.6, 16384x1024x1024 40.8 / 40.5, 8192x1024x4096 58.8 / 58.1.
+template <int TM, int TN, int RK, int NS, bool A_KC, bool B_KC, bool RAG = false>
 __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
   constexpr int NWAVES = n_waves(TM, TN);
   constexpr int WN = TN == 256 ? 4 : 2, WM = NWAVES / WN;         // wavefront grid
@@ -211,9 +214,9 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
   // column m0 of [k][ld]); every offset below stays far under 2^31 (checked on the host)
   const bf16* abase = A_KC ? p.A + (size_t)m0 * p.lda : p.A + m0;
   const bf16* bbase = B_KC ? p.B + (size_t)n0 * p.ldb : p.B + n0;
-  // (the view of a k-contiguous A ends with its last row: rows past it, of a last tile that is not full, read as zeros)
+  // (ragged: the view of A ends with its last row, rows past it read as zeros)
   const long long a_left = ((long long)(p.M - m0 - 1) * p.lda + p.K) * 2;
-  const int a_bytes = A_KC && a_left < 0x7fffffff ? (int)a_left : 0x7fffffff;
+  const int a_bytes = RAG && a_left < 0x7fffffff ? (int)a_left : 0x7fffffff;
   __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)abase, 0, a_bytes, 0x00020000);
   __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)bbase, 0, 0x7fffffff, 0x00020000);
   MoverA ma; ma.init(lane, p.lda);
@@ -221,17 +224,11 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
   FragsA fa; fa.init(lane, WTM * wm);
   FragsB fb; fb.init(lane, WTN * wn);
 
-  // the accumulators start from the bias of the lane's column, as those of gemm_phase.hip do: a product is the same bits
-  // whichever of these tiles it goes to
-  f32x16_t acc[MI][NI];
+  // The accumulators start from the bias of the lane's column, as those of gemm_phase.hip do: a product is the same bits
+  // whichever of these tiles it goes to.  (Fetched ahead of the operands and used behind the first barrier: nothing waits for it.)
+  float b0[NI];
 #pragma unroll
-  for (int j = 0; j < NI; ++j) {
-    const float b0 = p.epi.bias && p.splitk == 1 ? p.epi.bias[n0 + WTN * wn + 32 * j + (lane & 31)] : 0.f;
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = b0;
-  }
+  for (int j = 0; j < NI; ++j) b0[j] = p.epi.bias && p.splitk == 1 ? p.epi.bias[n0 + WTN * wn + 32 * j + (lane & 31)] : 0.f;
 
   // tile t lives in stage t % NS; indices past the end are clamped (their loads land in a stage nobody
   // reads any more), which keeps the count of loads in flight the same in every iteration
@@ -256,6 +253,14 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
   __builtin_amdgcn_s_barrier();               // ... and everybody's
   asm volatile("" ::: "memory");
   read_frags(0, 0, 0);
+
+  f32x16_t acc[MI][NI];
+#pragma unroll
+  for (int j = 0; j < NI; ++j)
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = b0[j];
 
   // One iteration = one k tile of RK.  Entering it, the step-0 fragments of tile t are on their way to
   // registers.  Tile t+NS-1 is requested into the stage tile t-1 occupied (every wavefront has passed
@@ -332,7 +337,7 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
     if (epilogue_reads_aux(e)) {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (mrow + 8 * i < p.M) raw[i] = load_aux8(e, mrow + 8 * i, n);
+        if (!RAG || mrow + 8 * i < p.M) raw[i] = load_aux8(e, mrow + 8 * i, n);
     }
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
@@ -348,7 +353,7 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         int row = 8 * i + (lane >> 3);
-        if (mrow + 8 * i >= p.M) continue;
+        if (RAG && mrow + 8 * i >= p.M) continue;
         float4 x0 = *reinterpret_cast<const float4*>(stage + row * EPI_LD + cc);
         float4 x1 = *reinterpret_cast<const float4*>(stage + row * EPI_LD + cc + 4);
         float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
@@ -360,9 +365,9 @@ __device__ __forceinline__ void ring_tile(const Params& p, const int wg) {
   }
 }
 
-template <int TM, int TN, int RK, int NS, bool A_KC, bool B_KC>
+template <int TM, int TN, int RK, int NS, bool A_KC, bool B_KC, bool RAG = false>
 __global__ void __launch_bounds__(64 * n_waves(TM, TN)) k_gemm_ring(Params p) {
-  ring_tile<TM, TN, RK, NS, A_KC, B_KC>(p, (int)blockIdx.x);
+  ring_tile<TM, TN, RK, NS, A_KC, B_KC, RAG>(p, (int)blockIdx.x);
 }
 // Several products of one operand layout in one launch: product g owns the workgroups first[g] .. first[g+1]-1.
 // Products too small to fill the chip one by one (the weight gradients of a layer) then need no split of their
@@ -401,21 +406,23 @@ MSLT_RING_INSTANCES(128, 128, 64)
 MSLT_RING_INSTANCES(256, 256, 32)
 MSLT_RING_INSTANCES(256, 128, 32)
 MSLT_RING_INSTANCES(128, 256, 32)
+template __global__ void k_gemm_ring<128, 256, 64, ring_depth(128, 256, 64), true, true, true>(Params);
+template __global__ void k_gemm_ring<128, 256, 64, ring_depth(128, 256, 64), true, false, true>(Params);
 #undef MSLT_RING_INSTANCES
 
-template <int TM, int TN, int RK, bool A_KC, bool B_KC>
+template <int TM, int TN, int RK, bool A_KC, bool B_KC, bool RAG = false>
 static hipError_t launch_one(const Params& p, dim3 grid, hipStream_t s) {
   constexpr int NS = ring_depth(TM, TN, RK);
   constexpr int LDS = lds_bytes(TM, TN, RK, NS);
   static_assert(LDS <= 160 * 1024, "LDS of a gfx950 compute unit");
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_ring<TM, TN, RK, NS, A_KC, B_KC>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_ring<TM, TN, RK, NS, A_KC, B_KC, RAG>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  k_gemm_ring<TM, TN, RK, NS, A_KC, B_KC><<<grid, dim3(64 * n_waves(TM, TN)), LDS, s>>>(p);
+  k_gemm_ring<TM, TN, RK, NS, A_KC, B_KC, RAG><<<grid, dim3(64 * n_waves(TM, TN)), LDS, s>>>(p);
   return hipGetLastError();
 }
 template <int TM, int TN, int RK>
@@ -485,7 +492,7 @@ bool gemm_ring_supported(const GemmDesc& d, int tile_m, int tile_n, int rk, bool
   if (!((tile_m == 256 && tile_n == 256) || (tile_m == 256 && tile_n == 128) || (tile_m == 128 && tile_n == 256) ||
         (tile_m == 128 && tile_n == 128 && rk == 64)))
     return false;
-  if ((d.M % tile_m && !(any_rows && d.a_kcontig)) || d.N % tile_n || d.K % rk) return false;
+  if ((d.M % tile_m && !(any_rows && d.a_kcontig && tile_m == 128 && tile_n == 256 && rk == 64)) || d.N % tile_n || d.K % rk) return false;
   // byte offsets inside a tile's buffer view stay below 2^31
   const long long a_span = d.a_kcontig ? (long long)tile_m * d.lda + d.K : (long long)d.K * d.lda + tile_m;
   const long long b_span = d.b_kcontig ? (long long)tile_n * d.ldb + d.K : (long long)d.K * d.ldb + tile_n;
@@ -512,7 +519,9 @@ hipError_t gemm_ring(const GemmDesc& d, int tile_m, int tile_n, int rk, int spli
   p.epi = d.epi;
   dim3 grid((unsigned)(p.tiles_m * p.tiles_n * splitk));
   hipError_t e;
-  if (rk == 64) {
+  if (d.M % tile_m) {
+    e = d.b_kcontig ? ring::launch_one<128, 256, 64, true, true, true>(p, grid, s) : ring::launch_one<128, 256, 64, true, false, true>(p, grid, s);
+  } else if (rk == 64) {
     if (tile_m == 256) e = ring::launch_layout<256, 128, 64>(d, p, grid, s);
     else if (tile_n == 256) e = ring::launch_layout<128, 256, 64>(d, p, grid, s);
     else e = ring::launch_layout<128, 128, 64>(d, p, grid, s);
