@@ -9,7 +9,7 @@
 // larger tile would buy nothing; what a wavefront alone on its SIMD loses is the latency of its slab, barrier to barrier.
 // The matrix pipes alone reach 134 TFLOP/s here, this kernel 92 where its rounds are full; against the guarded kernel
 // (four wavefronts, registers between global memory and LDS), us: 1024x768x768 22 / 27, 1024x768x3072 55 / 54 (both in
-// four parts), weight gradient 2304x768x1024 43 / 48, 1024x3072x768 52 / 53, 544x128x128 7.4 / 8.9.
+// four parts, which go to the guarded kernel: gemm_f32_pays), weight gradient 2304x768x1024 43 / 48, 1024x3072x768 52 / 53, 544x128x128 7.4 / 8.9.
 // Slabs go global memory -> LDS directly through a ring of five slots (16 KB: 64 rows of either operand), two workgroups on
 // a compute unit.  LDS and fragments are as in the guarded kernel: k-contiguous operands as [64 rows][32 k] with the
 // 16-byte chunks XOR-swizzled by the row, a lane's fragment being one 16-byte read for four matrix instructions, the

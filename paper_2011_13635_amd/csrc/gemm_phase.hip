@@ -5,8 +5,8 @@
 // other fetches its next fragments from LDS and queues loads, so that a SIMD's matrix core and its memory pipes are both
 // in use at any time.  A step of a wavefront is [queue loads, read fragments, wait for both the fragments and the loads
 // the next step reads] barrier [multiply] barrier, and the second group starts one barrier late.  In the kernel where
-// all wavefronts do the same thing at the same time (gemm_ring.hip) the matrix cores wait for every fragment read;
-// measured there 8192x8192x8192 took 810 us, here 690 (8192x4096x1024 87 -> 70, weight gradient 4096x3072x8192 193 -> 157).
+// all wavefronts do the same thing at the same time (gemm_ring.hip) the matrix cores wait for every fragment read: there
+// 8192x8192x8192 takes 842 us, here 757 (weight gradient 4096x3072x8192 183 and 169).
 //
 // Operands go global memory -> LDS directly (16 bytes per lane), into slots of 128 rows x 64 k (16 KB) that are refilled
 // as soon as both groups have read them, so that the loads in flight cover one and a half k tiles or more.  In LDS a
@@ -21,12 +21,13 @@
 // a result goes through LDS in its final type, 16 bytes per lane and whole cache lines per store (stores straight from
 // the registers, 32 bytes per row, took 4 us longer per tile).
 //
-// Tiles, and what they are for (microseconds, this tile / the best tile of gemm_ring.hip):
-//   256x256 (k_gemm_phase): 8192x4096x1024 with GELU 70 / 87; any operand layout.
-//   256x384 (k_gemm_wide): one round of workgroups where 256x256 tiles leave a second one half empty: 8192x3072x768 with
-//     GELU 43 / 63 (256x256 of this file 52), 8192x3072x1024 45 / 61 (53), 8192x2304x768 32 / 42 (37).
-//   256x128, four wavefronts, two workgroups on a compute unit (k_gemm_pair): outputs no multiple of 256 wide, 1280x30592x768 66 / 85.
-//   128x192 (k_gemm_slim): narrow outputs, 8192x768x3072 43 / 49.
+// Tiles, and what they are for (us, this tile / the best tile of gemm_ring.hip; all shapes and tiles side by side stand at
+// tile_plan in model.hip):
+//   256x256 (k_gemm_phase): 8192x4096x1024 64 / 69; any operand layout.
+//   256x384 (k_gemm_wide): one round of workgroups where 256x256 tiles leave a second one half empty: 8192x3072x768 38 / 48,
+//     8192x3072x1024 47 / 58, 8192x2304x768 33 / 42.
+//   256x128, four wavefronts, two workgroups on a compute unit (k_gemm_pair): outputs no multiple of 256 wide, 1280x30592x768 64 / 75.
+//   128x192 (k_gemm_slim): narrow outputs beside another chain of kernels.
 // M need not be a multiple of the tile (of anything, when A is k-contiguous): rows past the end are neither read nor written.
 #include "common.h"
 #include "gemm_epilogue.h"
@@ -649,8 +650,8 @@ __global__ void __launch_bounds__(256, 2) k_gemm_pair(Params p) {
 // ---- 128 x 192 ------------------------------------------------------------------------------------
 // Wavefront (wm, wn) of 4 x 2 owns 32 rows x 96 columns; one step is a whole k tile (A 16 KB, B 24 KB), four of which
 // fill the LDS and three are on their way.  Narrow tiles are bound by the loads that miss L2, about 50 GB/s a compute unit
-// (128x256 tiles at 8192x768x3072: 47 us; with the k tiles of the operands kept in L2 39, without any load 29, the loads
-// alone 45), so covering more compute units is worth more than a wider tile.  A k-strided B lies as three pieces of 64
+// (128x256 tiles at 8192x768x3072, operands from memory: 47 us; with their k tiles in L2, as in launches repeated on the
+// same operands, 39, without any load 29, the loads alone 45), so covering more compute units is worth more than a wider tile.  A k-strided B lies as three pieces of 64
 // columns, [64 k][64], chunk c of k row k in place c ^ (2 ((k>>1)&1)).
 constexpr int SLIM_C = 3, SLIM_TILE = SLOT + 8192 * SLIM_C, SLIM_BUFS = 4;
 template <bool B_KC>

@@ -1,6 +1,6 @@
 // Large-tile bf16 MFMA GEMM for gfx950: C(m,n) = sum_k A(m,k) B(n,k), fp32 accumulation, shared
 // epilogue.  A step takes the tiles of gemm_phase.hip where they are the faster ones, and from here 128x256 for narrow
-// outputs (8192x1024x1024 17 us, 128x192 of that file does not divide 1024, its 256x128 22) and 128x128 and 256x128 for the
+// outputs (8192x1024x1024 22 us, 128x192 of that file does not divide 1024, its 256x128 23) and 128x128 and 256x128 for the
 // weight gradients of smaller models.  Made for the products of the training step that have enough output tiles: the
 // operand feed (global memory -> vector L1 -> LDS) is what bounds a 128x128 tile, and a 256x256
 // tile moves half the bytes per MFMA.

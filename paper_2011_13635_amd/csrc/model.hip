@@ -699,23 +699,30 @@ static int layer_backward_end(mslt_model* m, int l) {
 
 // Tile of a product with a k-contiguous A for the large-tile kernels, or false when none takes it.  What counts is how
 // full the rounds of workgroups are (256 compute units; a 256x128 workgroup takes half of one) times what a tile shape
-// reaches when they are full, relative to 256x256.  The rates are those with which this rule agrees with the measured
-// order of the shapes, us:
+// reaches when they are full, relative to 256x256.  Products alone, launched back to back on the same normally distributed
+// operands (their values matter: on zeros 8192x8192x8192 takes 490 us instead of 757), us:
 //                           256x256  256x384  256x128  128x256  128x192
-//   8192x4096x1024 GELU          70        -       73       96        -
-//   8192x3072x1024               52       44       51       60       68
-//   8192x1024x4096               79        -       69       63        -
-//   8192x3072x768 GELU           56       44       49       64       71
-//   8192x2304x768                37       31       36       41       40
-//   8192x768x3072                63       99       54       49       44
-//   5504x3072x768                37       30       36       37       37
-//   5504x2304x768                20       28       23       25       36
-//   4096x3072x768 GELU           26       38       27       31       30
-//   1280x30592x768                -        -       65       84        -
-// The data gradient (k-strided B) keeps the order: 8192x4096x1024 58 / - / 65 / 87 / -, 8192x3072x768 45 / 37 / 42 / 53 / 62,
-// 8192x768x3072 61 / 100 / 54 / 45 / 46.
-// 128x128 is the register-staged kernel, two workgroups on a compute unit: 128x30592x768 25 us, 256x128 tiles half of
-// which lie past the end 28.
+//   8192x4096x1024 GELU          86        -       85       98        -
+//   8192x3072x1024               54       48       52       59       67
+//   8192x1024x4096               73        -       70       60        -
+//   8192x1024x1024               25        -       23       22        -
+//   8192x3072x768 GELU           62       51       55       65       71
+//   8192x2304x768                41       34       39       44       42
+//   8192x768x3072                53       84       51       39       41
+//   5504x3072x768                41       32       38       44       41
+//   5504x2304x768                23       30       25       30       39
+//   4096x3072x768 GELU           32       43       33       38       37
+//   1280x30592x768                -        -       65        -        -   (128x128 79)
+//   data gradient (k-strided B):
+//   8192x4096x1024               65        -       66       82        -
+//   8192x3072x768                43       39       44       50       57
+//   8192x768x3072                52       86       52       41       45
+//   8192x1024x4096               67        -       69       63        -
+// The rule takes the fastest of a row or one within 2 %, but for N = 768 with K = 3072, where 128x192 is ahead inside a step,
+// with cold operands and a second chain beside it (BERT-Base, without / with it: 9+3 layers with both objectives 64x128
+// 3847 / 3723 us, 3+3 layers 64x128 2557 / 2504, 9+3 16x512 3913 / 3787, 80x128 4183 / 4212).
+// 128x128 is the register-staged kernel, two workgroups on a compute unit: 128x30592x768 15 us, 256x128 tiles half of
+// which lie past the end 18.
 enum TileKernel { TILE_PHASE, TILE_RING, TILE_128 };
 struct TilePlan { TileKernel kernel; int tm, tn; double score; };
 static bool tile_plan(const GemmDesc& d, TilePlan* out) {
@@ -1182,7 +1189,9 @@ static int layer_backward_top(mslt_model* m, int l, const mslt_batch* bt, int T,
 //   halves of unequal rows: Base 9+3 3x128 1268 / 1336, 9x128 1582 / 1610, 23x128 2247 / 2436; Large 18+6 3x128 3001 / 3184,
 //   5x128 3414 / 3564, 13x200 6255 / 6554.
 // 512-wide models from 1.5 to 8 times the line are the exception (one chain ahead by up to 4 %: 7x128 750 / 726, 12x100 832 /
-// 809, but 3x512 920 / 945): no line by operations parts them from Base at 2x128.
+// 809, but 3x512 920 / 945): no line by operations parts them from Base at 2x128.  So is BERT-Large from 16384 rows on, where
+// one chain fills whole rounds (18+6 layers 32x512 19282 / 18788, 128x128 17710 / 17276, joint retraining 32x512 41844 / 41213;
+// but 16x512 10732 / 10933, Base 128x128 6026 / 6293).
 // Halves of unequal rows go as one chain also where the larger one has too many rows for the 32-wide few-tile kernel on
 // hidden-wide products while one chain would not leave the few-tile kernel: the chains then last as long as the one, and
 // share the chip.  Base 6+3 3x180 1372 / 1285, 5x112 1299 / 1223, 3x200 1376 / 1305, 5x128 1246 / 1211, 13x40 1229 / 1193; Large
