@@ -1197,11 +1197,15 @@ static int layer_backward_top(mslt_model* m, int l, const mslt_batch* bt, int T,
 // share the chip.  Base 6+3 3x180 1372 / 1285, 5x112 1299 / 1223, 3x200 1376 / 1305, 5x128 1246 / 1211, 13x40 1229 / 1193; Large
 // 6+3 3x140 1662 / 1571, 10x40 1549 / 1480; on either side 15x40 1189 / 1196 (320 rows each), 5x100 1189 / 1209, Large 3x128
 // 1415 / 1467 and 13x40 1598 / 1605.
+// And below BERT-Base's width up to twice the line, where kernels are short and the longer half decides: 4+2 layers, two / one,
+// 512-wide 5x128 718 / 689, 18x40 752 / 691, 7x100 755 / 708, 25x40 723 / 724; 384-wide 11x100 733 / 675; 256-wide 21x100 690 /
+// 666; 640-wide 9x40 735 / 682, 3x200 830 / 833; past it 512-wide 3x512 920 / 945, 640-wide 28x40 872 / 903.
 static bool plan_chains(const mslt_model* m, int B, int S, bool dropout, int (&rows)[2]) {
   const int T = B * S, Tr = m->mfma ? (int)rup(T, 128) : T, R1 = (B + 1) / 2 * S, R2 = Tr - R1;
   rows[0] = Tr; rows[1] = 0;
   if (m->dtype != 1 || !m->mfma || B < 2 || (dropout && (long long)R1 * m->nh * S % 4)) return false;
   if ((double)T * m->F * m->H <= (double)(1 << 29)) return false;
+  if (R1 != R2 && m->H < 768 && (double)T * m->F * m->H <= (double)(1 << 30)) return false;
   if (R1 != R2 && gemm_few_edge(std::max(R1, R2), m->H, m->H) != 32 && gemm_few_edge(Tr, m->F, m->H) && gemm_few_edge(Tr, m->H, m->F))
     return false;
   rows[0] = R1; rows[1] = R2;

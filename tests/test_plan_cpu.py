@@ -32,7 +32,9 @@ def test_fp32_products(M, N, K, akc, bkc, kernel, splitk):
     (768, 7, 100, (400, 368)), (768, 9, 128, (640, 512)), (768, 27, 203, (2842, 2662)), (768, 64, 128, (4096, 4096)),
     (1024, 3, 128, (256, 128)), (1024, 7, 64, (256, 256)), (1024, 13, 40, (280, 360)), (1024, 5, 128, (384, 256)),
     # one sequence, and products of at most 2^30 operations
-    (768, 1, 512, (512, 0)), (768, 1, 100, (128, 0)), (128, 64, 64, (4096, 0)), (512, 4, 128, (512, 0)), (512, 5, 128, (384, 256))])
+    (768, 1, 512, (512, 0)), (768, 1, 100, (128, 0)), (128, 64, 64, (4096, 0)), (512, 4, 128, (512, 0)),
+    # narrower than BERT-Base: unequal halves only from twice that on, equal ones as everywhere
+    (512, 5, 128, (640, 0)), (512, 25, 40, (1024, 0)), (640, 9, 40, (384, 0)), (512, 3, 512, (1024, 512)), (512, 6, 128, (384, 384))])
 def test_forward_chains(hidden, B, S, rows):
     base = synth.bert_base_shape(2).as_dict()
     base.update(hidden=hidden, ffn=4 * hidden, n_heads=hidden // 64)
